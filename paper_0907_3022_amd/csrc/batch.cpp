@@ -16,6 +16,7 @@
 #include "batch_internal.h"
 #include "internal.h"
 #include "pair.h"
+#include "pipe.h"
 
 namespace chebtd {
 int fail(Ctx *c, int code, const std::string &msg);
@@ -60,6 +61,16 @@ struct BatchState {
     std::vector<int64_t> deep_pair_off;
     DevBuf dblk_sys, dblk_wave0, dpblk_sys, dpblk_wave0, dtblk_sys, dtblk_tile;
     int64_t ndtail_blocks = 0;
+    // the deep schedule's passes as pipelined ones (pipe.h), unless a depth is
+    // forced: one launch per (pass, shape) over the systems it concerns
+    bool pipe_ok = false;
+    struct PipeLaunch {
+        int pass;
+        PipeShape shape;
+        int64_t off, count;
+    };
+    std::vector<PipeLaunch> pipe_launches;
+    DevBuf pblks, rw_dev;
     DevBuf head, done, flag;
     int64_t spin_limit = 0;  // wall-clock ticks a dependency wait may take
     hipGraphExec_t graph = nullptr;
@@ -91,7 +102,7 @@ void batch_destroy(Ctx *c)
     for (DevBuf *d : {&b->sys_dev, &b->gamma_dev, &b->work, &b->blk_sys, &b->blk_tile, &b->q_level_off,
                       &b->q_level_active, &b->q_tile_prefix, &b->q_order, &b->pblk_sys, &b->pblk_wave0,
                       &b->tblk_sys, &b->tblk_tile, &b->dblk_sys, &b->dblk_wave0, &b->dpblk_sys, &b->dpblk_wave0,
-                      &b->dtblk_sys, &b->dtblk_tile, &b->head, &b->done, &b->flag})
+                      &b->dtblk_sys, &b->dtblk_tile, &b->pblks, &b->rw_dev, &b->head, &b->done, &b->flag})
         release(*d);
     delete b;
     c->batch = nullptr;
@@ -103,6 +114,88 @@ static int upload(Ctx *c, DevBuf &d, const void *src, size_t bytes, const char *
     if (rc) return rc;
     hipError_t e = hipMemcpy(d.p, src, bytes, hipMemcpyHostToDevice);
     return e == hipSuccess ? CHEBTD_OK : hip_fail(c, e, what);
+}
+
+// Workgroup lists of the pipelined passes.  A pass over many systems has
+// workgroups enough with whole ribbons; otherwise the ribbons are cut into n
+// chunks each (8 rows or more), n with the least estimated time: the work
+// spread over the chip, but no less than the longest walk.  The longest walks
+// come first.
+static int build_pipe(Ctx *c, BatchState *b)
+{
+    const int ns = b->nsys;
+    int64_t total = 0;
+    for (int s = 0; s < ns; ++s) total += b->nsites[s];
+    std::vector<std::vector<PipeShape>> plan(ns);
+    size_t maxpass = 0;
+    for (int s = 0; s < ns; ++s) {
+        plan[s] = plan_pipe_shapes(total, b->M[s]);
+        if (plan[s].empty()) return CHEBTD_OK;  // pipe_ok stays false
+        maxpass = std::max(maxpass, plan[s].size());
+    }
+    std::vector<PipeBlk> blks;
+    std::vector<int32_t> k0(ns, 0);
+    std::vector<PipeShape> shapes;
+    for (const auto &p : plan)
+        for (const PipeShape &x : p)
+            if (std::none_of(shapes.begin(), shapes.end(),
+                             [&](const PipeShape &y) { return y.DW == x.DW && y.NW == x.NW; }))
+                shapes.push_back(x);
+    b->pipe_launches.clear();
+    for (size_t p = 0; p < maxpass; ++p) {
+        std::vector<int32_t> step(ns, 0);
+        for (const PipeShape &x : shapes) {
+            const int D = x.depth();
+            const int64_t slots = (int64_t)c->num_cus * (x.NW <= 4 ? 2 : 1);
+            std::vector<int32_t> ids;
+            for (int s = 0; s < ns; ++s)
+                if (p < plan[s].size() && plan[s][p].DW == x.DW && plan[s][p].NW == x.NW) ids.push_back(s);
+            if (ids.empty()) continue;
+            auto chunks = [&](int s, int n) {
+                return (int32_t)std::max(1, std::min(n, (b->sys[s].W - (D - 1)) / 8));
+            };
+            auto strips = [&](int s) {
+                return (int32_t)((b->sys[s].L + (int64_t)pipe_strip_cols(D) - 1) / pipe_strip_cols(D));
+            };
+            int best = 1;
+            double bt = 1e300;
+            for (int n = 1; n <= 64; ++n) {
+                double sum = 0.0, longest = 0.0;
+                bool more = n == 1;
+                for (int s : ids) {
+                    const int32_t m = chunks(s, n);
+                    more = more || m == n;
+                    const double it = pipe_iterations(x.DW, x.NW, b->sys[s].W, m);
+                    sum += it * strips(s) * m;
+                    longest = std::max(longest, it);
+                }
+                if (!more) break;
+                const double t = std::max(sum / (double)slots, x.NW <= 4 ? 0.6 * longest : longest);
+                if (t < 0.98 * bt) {
+                    bt = t;
+                    best = n;
+                }
+            }
+            std::vector<std::pair<int32_t, int32_t>> order;  // (-iterations, system)
+            for (int s : ids) order.push_back({-pipe_iterations(x.DW, x.NW, b->sys[s].W, chunks(s, best)), s});
+            std::stable_sort(order.begin(), order.end());
+            const int64_t off = (int64_t)blks.size();
+            for (const auto &o : order) {
+                const int s = o.second;
+                const int32_t m = chunks(s, best), W = b->sys[s].W;
+                for (int32_t st = 0; st < strips(s); ++st)
+                    for (int32_t q = 0; q < m; ++q)
+                        blks.push_back({s, st, pipe_row(q, m, W, D), pipe_row(q + 1, m, W, D), k0[s], 0});
+                step[s] = D;
+            }
+            b->pipe_launches.push_back({(int)p, x, off, (int64_t)blks.size() - off});
+        }
+        for (int s = 0; s < ns; ++s) k0[s] += step[s];
+    }
+    if ((int64_t)blks.size() > INT32_MAX) return fail(c, CHEBTD_E_ARG, "batch: too many workgroups");
+    int rc = upload(c, b->pblks, blks.data(), blks.size() * sizeof(PipeBlk), "pipelined workgroups");
+    b->pipe_ok = rc == CHEBTD_OK;
+    return rc;
 }
 
 // Rebuild the tile tables for the current tile size.
@@ -290,6 +383,15 @@ static hipError_t enqueue_step(Ctx *c, BatchState *b, hipStream_t s, int par)
                                  static_cast<const int32_t *>(b->tblk_tile.p), b->ntail_blocks, b->tile, par,
                                  b->block, 0);
     }
+    if (b->mode == CHEBTD_SCHED_DEEP && b->pipe_ok) {
+        const PipeBlk *pb = static_cast<const PipeBlk *>(b->pblks.p);
+        for (const auto &pl : b->pipe_launches) {
+            hipError_t e = launch_batch_pipe(s, pl.shape.DW, pl.shape.NW, sys, static_cast<const double *>(b->rw_dev.p),
+                                             pb + pl.off, pl.count, pl.pass, par);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     if (b->mode == CHEBTD_SCHED_DEEP) {
         const int32_t *dsys = static_cast<const int32_t *>(b->dblk_sys.p);
         const int32_t *dw = static_cast<const int32_t *>(b->dblk_wave0.p);
@@ -450,7 +552,7 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
     b->M.resize(nsys);
     b->nsites.resize(nsys);
     int64_t total = 0;
-    std::vector<double> g;
+    std::vector<double> g, r, rw;
     for (int s = 0; s < nsys; ++s) {
         const chebtd_sys_desc &d = descs[s];
         double a = 0, bb = 0;
@@ -473,6 +575,10 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         sd.off2 = -2.0 * d.t_hop / a;
         sd.gamma_off = (int64_t)b->gamma.size() / 2;
         b->gamma.insert(b->gamma.end(), g.begin(), g.end());
+        step_weights_real(a, bb, dt, M, r, &sd.phase);
+        sd.rw_off = (int64_t)rw.size();
+        rw.insert(rw.end(), r.begin(), r.end());
+        rw.resize(rw.size() + kMaxPipe, 0.0);
         b->M[s] = M;
         b->nsites[s] = d.width * d.length;
         total += b->nsites[s];
@@ -538,7 +644,9 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
     if ((rc = upload(c, b->gamma_dev, b->gamma.data(), b->gamma.size() * sizeof(double), "batch weights")) ||
         (rc = ensure(c, b->head, sizeof(int64_t), "queue head")) ||
         (rc = ensure(c, b->done, (size_t)nsys * sizeof(int32_t), "completion counters")) ||
-        (rc = ensure(c, b->flag, sizeof(int32_t), "timeout flag")) || (rc = build_tables(c, b))) {
+        (rc = ensure(c, b->flag, sizeof(int32_t), "timeout flag")) ||
+        (rc = upload(c, b->rw_dev, rw.data(), rw.size() * sizeof(double), "batch real weights")) ||
+        (b->deep_ok && !std::getenv("CHEBTD_BATCH_DEPTH") && (rc = build_pipe(c, b))) || (rc = build_tables(c, b))) {
         batch_destroy(c);
         return rc;
     }

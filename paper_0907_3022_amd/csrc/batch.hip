@@ -28,6 +28,7 @@
 #include "batch_internal.h"
 #include "device_ops.h"
 #include "deep_walk.h"
+#include "pipe_walk.h"
 #include "pair_walk.h"
 
 namespace chebtd {
@@ -239,6 +240,43 @@ __global__ __launch_bounds__(256) void k_batch_deep(const SysDev *__restrict__ s
         deep_wave<CHEBTD_ZIGZAG, D, HEAD, kDeepProp>(op, strip, chunk, A, nrm, en);
     else
         deep_wave<CHEBTD_ARMCHAIR, D, HEAD, kDeepProp>(op, strip, chunk, A, nrm, en);
+}
+
+// A pipelined pass of the listed workgroups (pipe_walk.h); a pass that
+// reaches the system's M is its last.  Buffers as in k_batch_deep.
+template <int DW, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_batch_pipe(const SysDev *__restrict__ sys,
+                                                           const double *__restrict__ rw,
+                                                           const PipeBlk *__restrict__ blks, int pass, int par)
+{
+    __shared__ PipeSlot slots[NW - 1][2];
+    const PipeBlk pb = blks[blockIdx.x];
+    const SysDev &sd = sys[pb.sys];
+    PipeOp op{};
+    op.onsite = sd.eps;
+    op.dshift = -sd.b;
+    op.s2 = sd.s2;
+    op.off2 = sd.off2;
+    op.W = sd.W;
+    op.L = sd.L;
+    double2 *cur = par ? sd.B : sd.psi;
+    double2 *nxt = par ? sd.psi : sd.B;
+    const bool odd = pass & 1, last = pb.k0 + DW * NW >= sd.M;
+    PipeArgs A{};
+    A.vkm1 = pass == 0 ? nullptr : odd ? sd.A : sd.D;
+    A.vk = pass == 0 || !odd ? cur : sd.C;
+    A.out1 = last ? nullptr : odd ? sd.D : sd.A;
+    A.out2 = last ? nullptr : odd ? cur : sd.C;
+    A.acc_in = nxt;
+    A.acc_out = nxt;
+    A.ckpt = nullptr;
+    A.fin = sd.phase;
+    A.r = rw + sd.rw_off + pb.k0;
+    double s0 = 0.0, s1 = 0.0;
+    if (sd.edge == CHEBTD_ZIGZAG)
+        pipe_block<CHEBTD_ZIGZAG, DW, NW>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
+    else
+        pipe_block<CHEBTD_ARMCHAIR, DW, NW>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
 }
 
 // The last order M of a system its passes left one short: v_M = 2 H~ v_{M-1}
@@ -459,6 +497,26 @@ hipError_t launch_batch_copy_back(hipStream_t s, const SysDev *sys, const int32_
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_batch_copy_back, dim3((unsigned)nblocks), dim3(block), 0, s, sys, blk_sys, blk_tile,
                        tile);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_pipe(hipStream_t s, int DW, int NW, const SysDev *sys, const double *rw, const PipeBlk *blks,
+                             int64_t nblocks, int pass, int par)
+{
+    if (nblocks == 0) return hipSuccess;
+    const dim3 grid((unsigned)nblocks), block(64 * NW);
+    if (DW == 2 && NW == 4)
+        hipLaunchKernelGGL((k_batch_pipe<2, 4>), grid, block, 0, s, sys, rw, blks, pass, par);
+    else if (DW == 3 && NW == 4)
+        hipLaunchKernelGGL((k_batch_pipe<3, 4>), grid, block, 0, s, sys, rw, blks, pass, par);
+    else if (DW == 4 && NW == 4)
+        hipLaunchKernelGGL((k_batch_pipe<4, 4>), grid, block, 0, s, sys, rw, blks, pass, par);
+    else if (DW == 5 && NW == 4)
+        hipLaunchKernelGGL((k_batch_pipe<5, 4>), grid, block, 0, s, sys, rw, blks, pass, par);
+    else if (DW == 3 && NW == 8)
+        hipLaunchKernelGGL((k_batch_pipe<3, 8>), grid, block, 0, s, sys, rw, blks, pass, par);
+    else
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

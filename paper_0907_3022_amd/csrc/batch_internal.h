@@ -29,6 +29,15 @@ struct SysDev {
     int32_t ndeep_ext;  // the first ndeep_ext of them take D + 1 orders
     int32_t kdeep;      // orders the deep passes cover
     int32_t drows_ext, dnstrips_ext, dnchunks_ext;  // the walk's grid at D + 1
+    // pipelined passes: the real weights (zeros past M) and e^{-ib dt}
+    int64_t rw_off;
+    double2 phase;
+};
+
+// One workgroup of a pipelined pass over the batch: its system, strip, rows,
+// and the order the pass starts from.
+struct PipeBlk {
+    int32_t sys, strip, ys, ye, k0, pad;
 };
 
 // Work queue of the persistent schedule (item = level, system, tile).
@@ -72,6 +81,10 @@ hipError_t launch_batch_tail(hipStream_t s, const SysDev *sys, const double2 *ga
 hipError_t launch_batch_clear_flag(hipStream_t s, int32_t *flag);
 // the deep schedule's passes for M orders at depth D (batch.cpp)
 void batch_deep_split(int M, int D, int *npass, int *next);
+// pipelined pass `pass` (DW orders in each of NW wavefronts) of the listed
+// workgroups; rw: the systems' real weights
+hipError_t launch_batch_pipe(hipStream_t s, int DW, int NW, const SysDev *sys, const double *rw, const PipeBlk *blks,
+                             int64_t nblocks, int pass, int par);
 hipError_t launch_batch_copy_back(hipStream_t s, const SysDev *sys, const int32_t *blk_sys,
                                   const int32_t *blk_tile, int64_t nblocks, int32_t tile, int block);
 

@@ -14,6 +14,13 @@ namespace chebtd {
 
 constexpr int kMaxDepth = 6;  // most Chebyshev orders one deep-walk pass carries
 
+// One pipelined pass (pipe.h): DW orders in each of a workgroup's NW wavefronts.
+struct PipeShape {
+    int DW, NW;
+    int chunks = 1;  // row chunks of the lattice
+    int depth() const { return DW * NW; }
+};
+
 // ---------------------------------------------------------------------------
 // Operators: each applies 2 H~ = (2/a)(H - b) to row i of a complex vector.
 // The step head needs H~ itself and takes exactly half (a power-of-two
@@ -125,6 +132,10 @@ struct Ctx {
     int M = 0;
     std::vector<double> gamma;  // interleaved complex, M+1 entries
     DevBuf gamma_dev;           // device copy of gamma
+    // gamma_k = phase (-i)^k rweight_k: J_0, 2 J_k and e^{-ib dt}
+    std::vector<double> rweight;
+    double2 phase = {1.0, 0.0};
+    const double *rweight_dev = nullptr;  // in gamma_dev, zeros past M
 
     // work vectors: two complex vectors of length n, two more for the
     // two-orders-per-pass kernel
@@ -136,6 +147,12 @@ struct Ctx {
     // kMaxDepth the deep kernel
     std::vector<int> passes;
     int deep_rows[kMaxDepth + 1] = {};  // rows per wavefront chunk of the deep kernel, by depth
+    // pipelined passes of one step (pipe.h): ribbons of M >= 2, unless a depth
+    // is forced; empty: the passes above run
+    std::vector<PipeShape> pipe;
+    int pipe_ring = 0;       // steps whose head partials are in flight
+    int64_t pipe_part = 0;   // doubles per step of them
+    DevBuf pipe_sums;        // [pipe_ring][pipe_part], then the last pass's norm partials
     // reduction scratch: partial sums, step counter, results
     DevBuf partials;   // double[2 * max_blocks]
     DevBuf results;    // double[16]
@@ -162,6 +179,8 @@ struct Ctx {
 int bessel_miller(double z, int kmax, std::vector<double> &J);
 int truncation_order(double z, double tol);
 void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma);
+// the same as real factors: gamma_k = phase (-i)^k r_k
+void step_weights_real(double a, double b, double dt, int M, std::vector<double> &r, double2 *phase);
 void shift_scale(double emin, double emax, double alpha, double *a, double *b);
 
 struct HolsteinCsr {

@@ -1,0 +1,235 @@
+// Pipelined many-order passes for single ribbons: kernel, pass plan and
+// launcher (the walk: pipe_walk.h), and the sums of the per-step norm and
+// energy partials.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+
+#include "device_ops.h"
+#include "internal.h"
+#include "pair.h"
+#include "pipe.h"
+#include "pipe_walk.h"
+
+namespace chebtd {
+
+template <int EDGE, int DW, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_pipe(PipeOp op, PipeArgs A, double *partials, double *knorm)
+{
+    __shared__ PipeSlot slots[NW - 1][2];
+    // consecutive chunks of a strip on one XCD, whose L2 then holds the halo
+    // rows that both read
+    const int32_t wg = logical_block(1);
+    const int32_t strip = wg / op.nchunks, chunk = wg - strip * op.nchunks;
+    const int32_t ys = pipe_row(chunk, op.nchunks, op.W, DW * NW);
+    const int32_t ye = pipe_row(chunk + 1, op.nchunks, op.W, DW * NW);
+    double s0 = 0.0, s1 = 0.0;
+    pipe_block<EDGE, DW, NW>(op, A, strip, ys, ye, slots, s0, s1);
+    const int w = pipe_wave<NW>(), lane = threadIdx.x & 63;
+    if (w == 0 && A.vkm1 == nullptr && partials) {
+        s0 = wave_sum(s0);
+        s1 = wave_sum(s1);
+        if (lane == 0) {
+            partials[2 * blockIdx.x] = s0;
+            partials[2 * blockIdx.x + 1] = s1;
+        }
+    }
+    if (w == NW - 1 && A.out2 == nullptr && knorm) {
+        s0 = wave_sum(s0);
+        if (lane == 0) knorm[blockIdx.x] = s0;
+    }
+}
+
+// Block b: step first + b's norm and energy; the last block also the final
+// norm.  Fixed order, as finalize_ne_block.
+__global__ __launch_bounds__(256) void k_ne_steps(NeSteps f)
+{
+    __shared__ double red[2 * 4];
+    const int64_t first = f.counter ? *f.counter : f.first;
+    __syncthreads();  // every thread has read the counter
+    const int nblk = gridDim.x;
+    for (int i = blockIdx.x; i < f.count; i += nblk) {
+        const double *p = f.partials + (int64_t)i * f.stride;
+        double s0 = 0.0, s1 = 0.0;
+        for (int q = threadIdx.x; q < f.nparts; q += blockDim.x) {
+            s0 += p[2 * q];
+            s1 += p[2 * q + 1];
+        }
+        block_sum2(s0, s1, red);
+        if (threadIdx.x == 0) {
+            if (f.norm_out) f.norm_out[first + i] = s0;
+            if (f.energy_out) f.energy_out[first + i] = f.a * s1 + f.b * s0;
+            if (f.check && f.first_step && i == 0) f.check[0] = s0;
+        }
+        __syncthreads();
+    }
+    if (f.knorm && f.check && (int)blockIdx.x == nblk - 1) {
+        double s0 = 0.0, z = 0.0;
+        for (int q = threadIdx.x; q < f.nk; q += blockDim.x) s0 += f.knorm[q];
+        block_sum2(s0, z, red);
+        if (threadIdx.x == 0) f.check[2] = s0;
+    }
+    if (f.counter && threadIdx.x == 0) *f.counter = first + f.count;  // one block
+}
+
+hipError_t launch_ne_steps(hipStream_t s, const NeSteps &f)
+{
+    const int nb = f.counter ? 1 : std::max(1, f.count);
+    hipLaunchKernelGGL(k_ne_steps, dim3((unsigned)nb), dim3(256), 0, s, f);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// plan
+// ---------------------------------------------------------------------------
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Iterations of the longest walk when W rows are cut into n chunks.
+int32_t pipe_iterations(int DW, int NW, int32_t W, int32_t n)
+{
+    int32_t most = 0;
+    for (int32_t c : {0, 1, n - 1}) {
+        if (c < 0 || c >= n) continue;
+        const int32_t ys = pipe_row(c, n, W, DW * NW), ye = pipe_row(c + 1, n, W, DW * NW);
+        for (int w = 0; w < NW; ++w) {
+            const pipedev::PipeSpan sp = pipedev::pipe_span(DW, NW, w, ys, ye, W);
+            most = std::max(most, sp.t0 + sp.n);
+        }
+    }
+    return most;
+}
+
+// Row chunks of a pass: the count with the least estimated time.  Taller
+// chunks repeat fewer halo rows, more chunks fill the CUs.  A CU holds two
+// workgroups of four wavefronts or one of eight; measured on MI355X an
+// iteration of a four-wavefront workgroup takes 0.44 us alone on its CU and
+// 0.74 us for two together (zigzag, five orders per wavefront: 128 x 8192 in
+// 2 / 3 / 5 chunks 52.8 / 63.5 / 55.5 us a step, 1024 x 32768 in 1 / 2 / 4 / 8
+// chunks 789 / 700 / 687 / 763 us).  CHEBTD_PIPE_CHUNKS overrides.
+static int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
+{
+    const int D = DW * NW;
+    const int64_t most = std::max<int64_t>(1, (W - (D - 1)) / 8);  // at least 8 rows each
+    if (const char *env = std::getenv("CHEBTD_PIPE_CHUNKS"))
+        return (int)std::max<int64_t>(1, std::min<int64_t>(most, std::atoi(env)));
+    const int64_t strips = ceil_div(L, pipe_strip_cols(D));
+    const int64_t slots = (int64_t)num_cus * (NW <= 4 ? 2 : 1);
+    int64_t best = 1;
+    double bt = 1e300;
+    const int64_t limit = std::min(most, std::max<int64_t>(1, 4 * slots / strips));
+    for (int64_t n = 1; n <= limit; ++n) {
+        const int64_t wgs = strips * n, rest = wgs % slots;
+        const double alone = NW <= 4 ? 0.6 : 1.0;
+        const double rounds = (double)(wgs / slots) + (rest == 0 ? 0.0 : rest <= num_cus ? alone : 1.0);
+        const double t = rounds * pipe_iterations(DW, NW, (int32_t)W, (int32_t)n);
+        if (t < bt) {
+            bt = t;
+            best = n;
+        }
+    }
+    return (int)best;
+}
+
+// Passes of a step of M orders, the last padded with orders of weight 0: the
+// cheapest by each pass's measured time (us, MI355X) on lattices of 10^4, 10^6
+// and 3.4 10^7 sites (10 x 1000 armchair, 128 x 8192 and 1024 x 32768 zigzag).
+// Not pipelined: lattices past the 32-bit offsets (deep_offsets_fit), and a
+// depth forced by CHEBTD_DEPTH.  CHEBTD_PIPE=DW,NW forces one shape, 0 none.
+std::vector<PipeShape> plan_pipe(const Ctx &c, int M)
+{
+    if (c.kind != HKind::Honeycomb || !deep_offsets_fit(c.W, c.L)) return {};
+    std::vector<PipeShape> out = plan_pipe_shapes(c.n, M);
+    for (size_t i = 0; i < out.size(); ++i)
+        out[i].chunks = i > 0 && out[i].DW == out[i - 1].DW && out[i].NW == out[i - 1].NW
+                            ? out[i - 1].chunks
+                            : pipe_chunks(c.W, c.L, out[i].DW, out[i].NW, c.num_cus);
+    return out;
+}
+
+std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M)
+{
+    std::vector<PipeShape> out;
+    if (M < 2 || std::getenv("CHEBTD_DEPTH")) return out;
+    struct Cand {
+        int DW, NW;
+        double tiny, small, large;
+    };
+    static const Cand cands[] = {{2, 4, 10.9, 26.0, 640.0}, {3, 4, 12.9, 32.0, 570.0}, {4, 4, 15.4, 41.0, 645.0},
+                                 {5, 4, 18.8, 53.0, 700.0}, {3, 8, 21.1, 62.0, 1090.0}};
+    int fdw = 0, fnw = 0;
+    if (const char *env = std::getenv("CHEBTD_PIPE"))
+        if (std::sscanf(env, "%d,%d", &fdw, &fnw) != 2) return out;
+    std::vector<double> best((size_t)M + 1, 1e300);
+    std::vector<int> from((size_t)M + 1, -1);
+    best[0] = 0.0;
+    for (int m = 1; m <= M; ++m)
+        for (int q = 0; q < (int)(sizeof cands / sizeof cands[0]); ++q) {
+            const Cand &x = cands[q];
+            if (fdw && (x.DW != fdw || x.NW != fnw)) continue;
+            const double t = best[(size_t)std::max(0, m - x.DW * x.NW)] +
+                             (sites < (int64_t(1) << 17) ? x.tiny : sites < (int64_t(1) << 22) ? x.small : x.large);
+            if (t < best[(size_t)m]) {
+                best[(size_t)m] = t;
+                from[(size_t)m] = q;
+            }
+        }
+    for (int m = M; m > 0;) {
+        if (from[(size_t)m] < 0) return {};
+        const Cand &x = cands[from[(size_t)m]];
+        out.push_back({x.DW, x.NW, 1});
+        m -= x.DW * x.NW;
+    }
+    // full passes first, so that only the last is padded: the depths in
+    // descending order hold M, and the last alone covers what is left
+    std::sort(out.begin(), out.end(), [](const PipeShape &a, const PipeShape &b) { return a.depth() > b.depth(); });
+    return out;
+}
+
+static PipeOp make_pipe_op(const Ctx &c, const PipeShape &sh)
+{
+    PipeOp op{};
+    op.onsite = c.eps;
+    op.dshift = -c.b;
+    op.s2 = 2.0 / c.a;
+    op.off2 = -2.0 * c.t_hop / c.a;
+    op.W = (int32_t)c.W;
+    op.L = (int32_t)c.L;
+    op.nstrips = (int32_t)ceil_div(c.L, pipe_strip_cols(sh.depth()));
+    op.nchunks = sh.chunks;
+    return op;
+}
+
+int64_t pipe_blocks(const Ctx &c, const PipeShape &sh)
+{
+    const PipeOp op = make_pipe_op(c, sh);
+    return (int64_t)op.nstrips * op.nchunks;
+}
+
+hipError_t launch_pipe(const Ctx &c, hipStream_t s, const PipeShape &sh, const PipeArgs &A, double *partials,
+                       double *knorm)
+{
+    const PipeOp op = make_pipe_op(c, sh);
+    const int64_t nb = (int64_t)op.nstrips * op.nchunks;
+    if (nb <= 0 || nb > INT32_MAX || !deep_offsets_fit(op.W, op.L)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nb), block(64 * sh.NW);
+    const bool zig = c.edge == CHEBTD_ZIGZAG;
+#define CHEBTD_PIPE_SHAPE(dw, nw)                                                                          \
+    if (sh.DW == dw && sh.NW == nw) {                                                                      \
+        if (zig)                                                                                           \
+            hipLaunchKernelGGL((k_pipe<CHEBTD_ZIGZAG, dw, nw>), grid, block, 0, s, op, A, partials, knorm); \
+        else                                                                                               \
+            hipLaunchKernelGGL((k_pipe<CHEBTD_ARMCHAIR, dw, nw>), grid, block, 0, s, op, A, partials, knorm); \
+        return hipGetLastError();                                                                          \
+    }
+    CHEBTD_PIPE_SHAPE(2, 4)
+    CHEBTD_PIPE_SHAPE(3, 4)
+    CHEBTD_PIPE_SHAPE(4, 4)
+    CHEBTD_PIPE_SHAPE(5, 4)
+    CHEBTD_PIPE_SHAPE(3, 8)
+#undef CHEBTD_PIPE_SHAPE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace chebtd

@@ -116,4 +116,12 @@ void step_weights(double a, double b, double dt, int M, std::vector<double> &gam
     }
 }
 
+void step_weights_real(double a, double b, double dt, int M, std::vector<double> &r, double2 *phase)
+{
+    bessel_miller(a * dt, M, r);
+    r.resize((size_t)M + 1);
+    for (int k = 1; k <= M; ++k) r[(size_t)k] *= 2.0;
+    *phase = make_double2(std::cos(b * dt), -std::sin(b * dt));
+}
+
 }  // namespace chebtd

@@ -11,6 +11,7 @@
 
 #include "internal.h"
 #include "pair.h"
+#include "pipe.h"
 
 namespace chebtd {
 int fail(Ctx *c, int code, const std::string &msg);
@@ -129,6 +130,78 @@ hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt,
     return k == c->M ? hipSuccess : hipErrorInvalidValue;
 }
 
+// Whether the steps run as pipelined passes.  ends: the step-end pairs are
+// wanted, which a padded last pass does not form.
+bool use_pipe(const Ctx &c, unsigned flags, bool ends)
+{
+    return !c.pipe.empty() && !(flags & CHEBTD_SINGLE_ORDER) && !ends;
+}
+
+// One time step cur -> nxt in pipelined passes; partials: the head's norm and
+// energy partials, knorm: the last pass's norm partials (or null).  Pass
+// outputs alternate between (vA, vC) and (vD, cur), as above.
+hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double *partials,
+                             double *knorm)
+{
+    double2 *X = nullptr, *Y = cur;
+    double2 *out[2][2] = {{static_cast<double2 *>(c->vA.p), static_cast<double2 *>(c->vC.p)},
+                          {static_cast<double2 *>(c->vD.p), cur}};
+    int k = 0;
+    for (size_t i = 0; i < c->pipe.size(); ++i) {
+        const PipeShape &sh = c->pipe[i];
+        const bool last = i + 1 == c->pipe.size();
+        PipeArgs A{};
+        A.vkm1 = X;
+        A.vk = Y;
+        A.out1 = last ? nullptr : out[i & 1][0];
+        A.out2 = last ? nullptr : out[i & 1][1];
+        A.acc_in = nxt;
+        A.acc_out = nxt;
+        A.ckpt = i == 0 ? ckpt : nullptr;
+        A.fin = c->phase;
+        A.r = c->rweight_dev + k;
+        hipError_t e = launch_pipe(*c, s, sh, A, partials, last ? knorm : nullptr);
+        if (e != hipSuccess) return e;
+        X = A.out1;
+        Y = A.out2;
+        k += sh.depth();
+    }
+    return k >= c->M ? hipSuccess : hipErrorInvalidValue;
+}
+
+// K pipelined steps from P, alternating with vB.  norm and energy of the
+// steps are summed several steps at a time; check (host-visible, or null)
+// receives the norms before the first step and after the last.
+// on-site values of step st: onsite + st * stride, or (null) the context's.
+hipError_t run_pipe(Ctx *c, hipStream_t s, double2 *P, int64_t K, bool keep, const double *onsite, int64_t stride,
+                    double *norm_out, double *energy_out, double *check)
+{
+    double2 *B = static_cast<double2 *>(c->vB.p);
+    double *sums = static_cast<double *>(c->pipe_sums.p);
+    double *knorm = sums + (size_t)c->pipe_ring * (size_t)c->pipe_part;
+    const double *saved = c->eps;
+    hipError_t e = hipSuccess;
+    int64_t first = 0;
+    for (int64_t st = 0; st < K && e == hipSuccess; ++st) {
+        if (onsite) c->eps = onsite + st * stride;
+        const int64_t slot = st - first;
+        const bool last = st + 1 == K;
+        e = enqueue_step_pipe(c, s, (st & 1) ? B : P, (st & 1) ? P : B, keep ? adj_checkpoint(c, st, K) : nullptr,
+                              sums + slot * c->pipe_part, last && check ? knorm : nullptr);
+        const bool wanted = norm_out || energy_out || (check && (first == 0 || last));
+        if (e == hipSuccess && (last || slot + 1 == c->pipe_ring)) {
+            const NeSteps f{sums, c->pipe_part, (int)(c->pipe_part / 2), (int)(slot + 1), c->a, c->b, norm_out,
+                            energy_out, first, nullptr, last && check ? knorm : nullptr,
+                            (int)pipe_blocks(*c, c->pipe.back()), check, first == 0};
+            if (wanted) e = launch_ne_steps(s, f);
+            first = st + 1;
+        }
+    }
+    c->eps = saved;
+    if (e == hipSuccess && (K & 1)) e = launch_copy(s, B, P, c->n);
+    return e;
+}
+
 // Enqueue one time step: cur -> nxt.  cur is overwritten with v_2, v_4, ...
 hipError_t enqueue_step(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double2 *ends,
                         double *norm_out, double *energy_out, unsigned flags)
@@ -200,9 +273,21 @@ int get_pair_graph(Ctx *c, double2 *psi, double *norm_out, double *energy_out, u
     hipGraph_t g = nullptr;
     e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
-    hipError_t e1 = enqueue_step(c, c->cap_stream, psi, B, nullptr, nullptr, norm_out, energy_out, flags);
-    hipError_t e2 = e1 == hipSuccess ? enqueue_step(c, c->cap_stream, B, psi, nullptr, nullptr, norm_out, energy_out, flags)
-                                     : e1;
+    hipError_t e1, e2;
+    if (use_pipe(*c, flags, false)) {
+        double *sums = static_cast<double *>(c->pipe_sums.p);
+        e1 = enqueue_step_pipe(c, c->cap_stream, psi, B, nullptr, sums, nullptr);
+        e2 = e1 == hipSuccess ? enqueue_step_pipe(c, c->cap_stream, B, psi, nullptr, sums + c->pipe_part, nullptr) : e1;
+        if (e2 == hipSuccess && (norm_out || energy_out))
+            e2 = launch_ne_steps(c->cap_stream, {sums, c->pipe_part, (int)(c->pipe_part / 2), 2, c->a, c->b, norm_out,
+                                                 energy_out, 0, static_cast<int64_t *>(c->counter.p), nullptr, 0,
+                                                 nullptr, 0});
+    } else {
+        e1 = enqueue_step(c, c->cap_stream, psi, B, nullptr, nullptr, norm_out, energy_out, flags);
+        e2 = e1 == hipSuccess
+                 ? enqueue_step(c, c->cap_stream, B, psi, nullptr, nullptr, norm_out, energy_out, flags)
+                 : e1;
+    }
     e = hipStreamEndCapture(c->cap_stream, &g);
     if (e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -244,11 +329,13 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     double2 *B = static_cast<double2 *>(c->vB.p);
     hipError_t e = hipSuccess;
 
-    if (check) {
+    // pipelined steps sum the norms of the check themselves
+    const bool pipe = use_pipe(*c, flags, keep && adj_step_ends(c, 0)) && ((flags & CHEBTD_GRAPH) == 0 || keep);
+    if (check && !pipe) {
         e = enqueue_norm(c, s, P, 0);
         if (e != hipSuccess) return hip_fail(c, e, "initial norm");
     }
-    if (norm_dev || energy_dev) {
+    if ((norm_dev || energy_dev) && !pipe) {
         e = launch_reset_counter(s, static_cast<int64_t *>(c->counter.p));
         if (e != hipSuccess) return hip_fail(c, e, "counter reset");
     }
@@ -260,6 +347,9 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
         e = launch_chain_small(*c, s, P, P, static_cast<const double2 *>(c->gamma_dev.p), K, norm_dev,
                                energy_dev, keep ? adj_checkpoint(c, 0, K) : nullptr);
         if (e != hipSuccess) return hip_fail(c, e, "persistent chain kernel");
+    } else if (pipe) {
+        e = run_pipe(c, s, P, K, keep, nullptr, 0, norm_dev, energy_dev, check ? c->pinned : nullptr);
+        if (e != hipSuccess) return hip_fail(c, e, "pipelined steps");
     } else if ((flags & CHEBTD_GRAPH) && !keep) {
         hipGraphExec_t ge = nullptr;
         int rc = get_pair_graph(c, P, norm_dev, energy_dev, flags, &ge);
@@ -269,7 +359,15 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
             if (e != hipSuccess) return hip_fail(c, e, "hipGraphLaunch");
         }
         if (K & 1) {
-            e = enqueue_step(c, s, P, B, nullptr, nullptr, norm_dev, energy_dev, flags);
+            if (use_pipe(*c, flags, false)) {
+                double *sums = static_cast<double *>(c->pipe_sums.p);
+                e = enqueue_step_pipe(c, s, P, B, nullptr, sums, nullptr);
+                if (e == hipSuccess && (norm_dev || energy_dev))
+                    e = launch_ne_steps(s, {sums, c->pipe_part, (int)(c->pipe_part / 2), 1, c->a, c->b, norm_dev,
+                                            energy_dev, K - 1, nullptr, nullptr, 0, nullptr, 0});
+            } else {
+                e = enqueue_step(c, s, P, B, nullptr, nullptr, norm_dev, energy_dev, flags);
+            }
             if (e == hipSuccess) e = launch_copy(s, B, P, c->n);
             if (e != hipSuccess) return hip_fail(c, e, "last step");
         }
@@ -288,9 +386,11 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     }
 
     if (!check) return CHEBTD_OK;
-    e = enqueue_norm(c, s, P, 2);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->pinned, c->results.p, 4 * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (!pipe) {
+        e = enqueue_norm(c, s, P, 2);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(c->pinned, c->results.p, 4 * sizeof(double), hipMemcpyDeviceToHost, s);
+    }
     // the several-workgroup chain run's wait limit
     int32_t *tflag = small ? chain_multi_timeout(*c) : nullptr;
     if (e == hipSuccess && tflag) e = hipMemcpyAsync(c->pinned + 8, tflag, sizeof(int32_t), hipMemcpyDeviceToHost, s);
@@ -336,9 +436,11 @@ int chebtd_propagate_td(chebtd_ctx *ctx, double *psi_dev, int64_t K, const doubl
     double2 *B = static_cast<double2 *>(c->vB.p);
     hipError_t e = hipSuccess;
     const bool check = (flags & CHEBTD_NO_CHECK) == 0;
-    if (check) e = enqueue_norm(c, s, P, 0);
-    if (e == hipSuccess && (norm_dev || energy_dev)) e = launch_reset_counter(s, static_cast<int64_t *>(c->counter.p));
-    for (int64_t st = 0; st < K && e == hipSuccess; ++st) {
+    const bool pipe = use_pipe(*c, flags, false);
+    if (pipe) e = run_pipe(c, s, P, K, false, onsite_dev, stride, norm_dev, energy_dev, check ? c->pinned : nullptr);
+    if (check && !pipe) e = enqueue_norm(c, s, P, 0);
+    if (!pipe && e == hipSuccess && (norm_dev || energy_dev)) e = launch_reset_counter(s, static_cast<int64_t *>(c->counter.p));
+    for (int64_t st = 0; st < K && e == hipSuccess && !pipe; ++st) {
         const double *on = onsite_dev + st * stride;
         if (c->kind == HKind::Chain)
             c->V = on;
@@ -355,12 +457,14 @@ int chebtd_propagate_td(chebtd_ctx *ctx, double *psi_dev, int64_t K, const doubl
     else if (c->kind == HKind::Honeycomb)
         c->eps = saved;
     c->hol_delta = nullptr;
-    if (e == hipSuccess && (K & 1)) e = launch_copy(s, B, P, c->n);
+    if (e == hipSuccess && (K & 1) && !pipe) e = launch_copy(s, B, P, c->n);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_propagate_td");
     if (!check) return CHEBTD_OK;
-    e = enqueue_norm(c, s, P, 2);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(c->pinned, c->results.p, 4 * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (!pipe) {
+        e = enqueue_norm(c, s, P, 2);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(c->pinned, c->results.p, 4 * sizeof(double), hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(c, e, "norm check");
     const double n0 = c->pinned[0], n1 = c->pinned[2];
