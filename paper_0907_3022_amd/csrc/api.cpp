@@ -10,6 +10,7 @@
 #include <string>
 
 #include "internal.h"
+#include "chain_tile.h"
 #include "pair.h"
 #include "pipe.h"
 
@@ -253,7 +254,7 @@ int chebtd_destroy(chebtd_ctx *ctx)
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (DevBuf *b : {&c->vA, &c->vB, &c->vC, &c->vD, &c->partials, &c->results, &c->counter, &c->gamma_dev,
                       &c->hol_occ, &c->hol_up, &c->hol_dn,
-                      &c->hol_tot, &c->hol_site, &c->hol_binom, &c->chainx, &c->pipe_sums})
+                      &c->hol_tot, &c->hol_site, &c->hol_binom, &c->chainx})
         release(*b);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->ev_a) (void)hipEventDestroy(c->ev_a);
@@ -511,20 +512,34 @@ int chebtd_set_bounds(chebtd_ctx *ctx, double emin, double emax, double alpha)
 
 static int plan_common(Ctx *c, double dt, int M)
 {
-    step_weights(c->a, c->b, dt, M, c->gamma);
-    step_weights_real(c->a, c->b, dt, M, c->rweight, &c->phase);
+    step_weights(c->a, c->b, dt, M, c->gamma, c->rweight, &c->phase);
     int rc;
     // one upload: gamma, then the real factors padded for a last pass past M
     std::vector<double> up(c->gamma);
     up.insert(up.end(), c->rweight.begin(), c->rweight.end());
-    up.resize(up.size() + kMaxPipe, 0.0);
+    up.resize(up.size() + std::max(kMaxPipe, kTilePad), 0.0);
     if ((rc = ensure(c, c->gamma_dev, up.size() * sizeof(double), "weights"))) return rc;
     c->rweight_dev = static_cast<const double *>(c->gamma_dev.p) + c->gamma.size();
     hipError_t e = hipMemcpy(c->gamma_dev.p, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_plan upload");
     const size_t vbytes = (size_t)c->n * 2 * sizeof(double);
-    if ((rc = ensure(c, c->vA, vbytes, "work vector A")) || (rc = ensure(c, c->vB, vbytes, "work vector B")))
+    // pipelined or tiled steps: behind vB the head partials of up to 32 steps
+    // (4 MiB at most, or two steps), then a norm partial per block of the last
+    // pass
+    c->pipe = plan_pipe(*c, M);
+    c->tile = plan_tile(*c, M);
+    size_t sums = 0;
+    if (!c->pipe.empty() || c->tile.R) {
+        const int64_t nb = c->tile.R ? tile_blocks(*c, c->tile.R, c->tile.depths.front()) : pipe_blocks(*c, c->pipe.front());
+        const int64_t nl = c->tile.R ? tile_blocks(*c, c->tile.R, c->tile.depths.back()) : pipe_blocks(*c, c->pipe.back());
+        c->pipe_last = (int)nl;
+        c->pipe_part = 2 * nb;
+        c->pipe_ring = (int)std::max<int64_t>(2, std::min<int64_t>(32, (int64_t(4) << 20) / (16 * nb)));
+        sums = ((size_t)c->pipe_ring * (size_t)c->pipe_part + (size_t)nl) * sizeof(double);
+    }
+    if ((rc = ensure(c, c->vA, vbytes, "work vector A")) || (rc = ensure(c, c->vB, vbytes + sums, "work vector B")))
         return rc;
+    c->pipe_sums = reinterpret_cast<double *>(static_cast<char *>(c->vB.p) + vbytes);
     // two more vectors let brick-wall Hamiltonians advance two orders per pass
     c->use_pairs = false;
     c->passes.clear();
@@ -537,16 +552,6 @@ static int plan_common(Ctx *c, double dt, int M)
         for (int d = 3; d <= kMaxDepth; ++d) c->deep_rows[d] = choose_deep_rows(*c, d);
     }
     if ((rc = ensure_partials(c))) return rc;
-    c->pipe = plan_pipe(*c, M);
-    if (!c->pipe.empty()) {
-        // head partials of up to 32 steps (4 MiB at most, or two steps), then
-        // one norm partial per block of the last pass
-        const int64_t nb = pipe_blocks(*c, c->pipe.front()), nl = pipe_blocks(*c, c->pipe.back());
-        c->pipe_part = 2 * nb;
-        c->pipe_ring = (int)std::max<int64_t>(2, std::min<int64_t>(32, (int64_t(4) << 20) / (16 * nb)));
-        const size_t bytes = ((size_t)c->pipe_ring * (size_t)c->pipe_part + (size_t)nl) * sizeof(double);
-        if ((rc = ensure(c, c->pipe_sums, bytes, "step sums"))) return rc;
-    }
     if (c->kind == HKind::Chain) {
         const size_t xb = chain_multi_scratch_bytes(chain_multi_config(c->n));
         if (xb && (rc = ensure(c, c->chainx, xb, "chain exchange scratch"))) return rc;

@@ -159,7 +159,7 @@ static int build_pipe(Ctx *c, BatchState *b)
             };
             int best = 1;
             double bt = 1e300;
-            for (int n = 1; n <= 64; ++n) {
+            for (int n = 1; n <= 16; ++n) {
                 double sum = 0.0, longest = 0.0;
                 bool more = n == 1;
                 for (int s : ids) {
@@ -174,6 +174,8 @@ static int build_pipe(Ctx *c, BatchState *b)
                 if (t < 0.98 * bt) {
                     bt = t;
                     best = n;
+                } else if (t > 1.2 * bt) {
+                    break;  // more chunks only repeat more halo rows
                 }
             }
             std::vector<std::pair<int32_t, int32_t>> order;  // (-iterations, system)
@@ -562,8 +564,8 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
             batch_destroy(c);
             return fail(c, CHEBTD_E_ARG, "chebtd_batch_create: bad a*dt for system " + std::to_string(s));
         }
-        step_weights(a, bb, dt, M, g);
         SysDev &sd = b->sys[s];
+        step_weights(a, bb, dt, M, g, r, &sd.phase);
         sd.eps = d.eps_dev;
         sd.psi = reinterpret_cast<double2 *>(d.psi_dev);
         sd.W = (int32_t)d.width;
@@ -575,7 +577,6 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         sd.off2 = -2.0 * d.t_hop / a;
         sd.gamma_off = (int64_t)b->gamma.size() / 2;
         b->gamma.insert(b->gamma.end(), g.begin(), g.end());
-        step_weights_real(a, bb, dt, M, r, &sd.phase);
         sd.rw_off = (int64_t)rw.size();
         rw.insert(rw.end(), r.begin(), r.end());
         rw.resize(rw.size() + kMaxPipe, 0.0);

@@ -21,6 +21,12 @@ struct PipeShape {
     int depth() const { return DW * NW; }
 };
 
+// Tiled passes over a chain (chain_tile.h): R sites per lane, orders per pass.
+struct TilePlan {
+    int R = 0;
+    std::vector<int> depths;
+};
+
 // ---------------------------------------------------------------------------
 // Operators: each applies 2 H~ = (2/a)(H - b) to row i of a complex vector.
 // The step head needs H~ itself and takes exactly half (a power-of-two
@@ -150,9 +156,11 @@ struct Ctx {
     // pipelined passes of one step (pipe.h): ribbons of M >= 2, unless a depth
     // is forced; empty: the passes above run
     std::vector<PipeShape> pipe;
+    TilePlan tile;           // the same for chains
     int pipe_ring = 0;       // steps whose head partials are in flight
     int64_t pipe_part = 0;   // doubles per step of them
-    DevBuf pipe_sums;        // [pipe_ring][pipe_part], then the last pass's norm partials
+    int pipe_last = 0;       // blocks of a step's last pass
+    double *pipe_sums = nullptr;  // [pipe_ring][pipe_part], then the last pass's norm partials (behind vB)
     // reduction scratch: partial sums, step counter, results
     DevBuf partials;   // double[2 * max_blocks]
     DevBuf results;    // double[16]
@@ -179,8 +187,9 @@ struct Ctx {
 int bessel_miller(double z, int kmax, std::vector<double> &J);
 int truncation_order(double z, double tol);
 void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma);
-// the same as real factors: gamma_k = phase (-i)^k r_k
-void step_weights_real(double a, double b, double dt, int M, std::vector<double> &r, double2 *phase);
+// and as real factors: gamma_k = phase (-i)^k r_k
+void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma, std::vector<double> &r,
+                  double2 *phase);
 void shift_scale(double emin, double emax, double alpha, double *a, double *b);
 
 struct HolsteinCsr {

@@ -99,10 +99,11 @@ void shift_scale(double emin, double emax, double alpha, double *a, double *b)
     *a = 0.5 * (emax - emin + eps);
 }
 
-// gamma_0 = e^{-i b dt} J_0(a dt), gamma_k = 2 e^{-i b dt} (-i)^k J_k(a dt).
-void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma)
+// gamma_0 = e^{-i b dt} J_0(a dt), gamma_k = 2 e^{-i b dt} (-i)^k J_k(a dt);
+// r: J_0, 2 J_k.
+void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma, std::vector<double> &J,
+                  double2 *phase_out)
 {
-    std::vector<double> J;
     bessel_miller(a * dt, M, J);
     const std::complex<double> phase(std::cos(b * dt), -std::sin(b * dt));
     static const std::complex<double> minus_i_pow[4] = {
@@ -113,15 +114,17 @@ void step_weights(double a, double b, double dt, int M, std::vector<double> &gam
         if (k) g *= 2.0;
         gamma[2 * (size_t)k] = g.real();
         gamma[2 * (size_t)k + 1] = g.imag();
+        if (k) J[(size_t)k] *= 2.0;
     }
+    J.resize((size_t)M + 1);
+    *phase_out = make_double2(phase.real(), phase.imag());
 }
 
-void step_weights_real(double a, double b, double dt, int M, std::vector<double> &r, double2 *phase)
+void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma)
 {
-    bessel_miller(a * dt, M, r);
-    r.resize((size_t)M + 1);
-    for (int k = 1; k <= M; ++k) r[(size_t)k] *= 2.0;
-    *phase = make_double2(std::cos(b * dt), -std::sin(b * dt));
+    std::vector<double> r;
+    double2 phase;
+    step_weights(a, b, dt, M, gamma, r, &phase);
 }
 
 }  // namespace chebtd

@@ -10,6 +10,7 @@
 #include <string>
 
 #include "internal.h"
+#include "chain_tile.h"
 #include "pair.h"
 #include "pipe.h"
 
@@ -130,23 +131,47 @@ hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt,
     return k == c->M ? hipSuccess : hipErrorInvalidValue;
 }
 
-// Whether the steps run as pipelined passes.  ends: the step-end pairs are
-// wanted, which a padded last pass does not form.
+// Whether the steps run as pipelined (ribbons) or tiled (chains) passes.
+// ends: the step-end pairs are wanted, which a padded last pipelined pass does
+// not form.
 bool use_pipe(const Ctx &c, unsigned flags, bool ends)
 {
-    return !c.pipe.empty() && !(flags & CHEBTD_SINGLE_ORDER) && !ends;
+    return (c.tile.R || (!c.pipe.empty() && !ends)) && !(flags & CHEBTD_SINGLE_ORDER);
 }
 
 // One time step cur -> nxt in pipelined passes; partials: the head's norm and
 // energy partials, knorm: the last pass's norm partials (or null).  Pass
 // outputs alternate between (vA, vC) and (vD, cur), as above.
-hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double *partials,
-                             double *knorm)
+// ends (or null; chains): 2 n values that receive v_{M-1}, v_M.
+hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double2 *ends,
+                             double *partials, double *knorm)
 {
     double2 *X = nullptr, *Y = cur;
     double2 *out[2][2] = {{static_cast<double2 *>(c->vA.p), static_cast<double2 *>(c->vC.p)},
                           {static_cast<double2 *>(c->vD.p), cur}};
     int k = 0;
+    for (size_t i = 0; c->tile.R && i < c->tile.depths.size(); ++i) {
+        const bool last = i + 1 == c->tile.depths.size();
+        TileArgs A{};
+        A.vkm1 = X;
+        A.vk = Y;
+        A.out1 = !last ? out[i & 1][0] : ends;
+        A.out2 = !last ? out[i & 1][1] : ends ? ends + c->n : nullptr;
+        A.acc_in = nxt;
+        A.acc_out = nxt;
+        A.ckpt = i == 0 ? ckpt : nullptr;
+        A.fin = last ? c->phase : make_double2(1.0, 0.0);
+        A.r = c->rweight_dev + k;
+        A.D = c->tile.depths[i];
+        A.k0 = k;
+        hipError_t e = launch_tile(*c, s, c->tile.R, A, partials, last ? knorm : nullptr);
+        if (e != hipSuccess) return e;
+        X = A.out1;
+        Y = A.out2;
+        k += A.D;
+    }
+    if (c->tile.R) return k == c->M ? hipSuccess : hipErrorInvalidValue;
+    if (ends) return hipErrorInvalidValue;
     for (size_t i = 0; i < c->pipe.size(); ++i) {
         const PipeShape &sh = c->pipe[i];
         const bool last = i + 1 == c->pipe.size();
@@ -177,27 +202,29 @@ hipError_t run_pipe(Ctx *c, hipStream_t s, double2 *P, int64_t K, bool keep, con
                     double *norm_out, double *energy_out, double *check)
 {
     double2 *B = static_cast<double2 *>(c->vB.p);
-    double *sums = static_cast<double *>(c->pipe_sums.p);
+    double *sums = c->pipe_sums;
     double *knorm = sums + (size_t)c->pipe_ring * (size_t)c->pipe_part;
-    const double *saved = c->eps;
+    const double **site = c->kind == HKind::Chain ? &c->V : &c->eps;
+    const double *saved = *site;
     hipError_t e = hipSuccess;
     int64_t first = 0;
     for (int64_t st = 0; st < K && e == hipSuccess; ++st) {
-        if (onsite) c->eps = onsite + st * stride;
+        if (onsite) *site = onsite + st * stride;
         const int64_t slot = st - first;
         const bool last = st + 1 == K;
         e = enqueue_step_pipe(c, s, (st & 1) ? B : P, (st & 1) ? P : B, keep ? adj_checkpoint(c, st, K) : nullptr,
-                              sums + slot * c->pipe_part, last && check ? knorm : nullptr);
+                              keep ? adj_step_ends(c, st) : nullptr, sums + slot * c->pipe_part,
+                              last && check ? knorm : nullptr);
         const bool wanted = norm_out || energy_out || (check && (first == 0 || last));
         if (e == hipSuccess && (last || slot + 1 == c->pipe_ring)) {
             const NeSteps f{sums, c->pipe_part, (int)(c->pipe_part / 2), (int)(slot + 1), c->a, c->b, norm_out,
                             energy_out, first, nullptr, last && check ? knorm : nullptr,
-                            (int)pipe_blocks(*c, c->pipe.back()), check, first == 0};
+                            c->pipe_last, check, first == 0};
             if (wanted) e = launch_ne_steps(s, f);
             first = st + 1;
         }
     }
-    c->eps = saved;
+    *site = saved;
     if (e == hipSuccess && (K & 1)) e = launch_copy(s, B, P, c->n);
     return e;
 }
@@ -275,9 +302,9 @@ int get_pair_graph(Ctx *c, double2 *psi, double *norm_out, double *energy_out, u
     if (e != hipSuccess) return hip_fail(c, e, "hipStreamBeginCapture");
     hipError_t e1, e2;
     if (use_pipe(*c, flags, false)) {
-        double *sums = static_cast<double *>(c->pipe_sums.p);
-        e1 = enqueue_step_pipe(c, c->cap_stream, psi, B, nullptr, sums, nullptr);
-        e2 = e1 == hipSuccess ? enqueue_step_pipe(c, c->cap_stream, B, psi, nullptr, sums + c->pipe_part, nullptr) : e1;
+        double *sums = c->pipe_sums;
+        e1 = enqueue_step_pipe(c, c->cap_stream, psi, B, nullptr, nullptr, sums, nullptr);
+        e2 = e1 == hipSuccess ? enqueue_step_pipe(c, c->cap_stream, B, psi, nullptr, nullptr, sums + c->pipe_part, nullptr) : e1;
         if (e2 == hipSuccess && (norm_out || energy_out))
             e2 = launch_ne_steps(c->cap_stream, {sums, c->pipe_part, (int)(c->pipe_part / 2), 2, c->a, c->b, norm_out,
                                                  energy_out, 0, static_cast<int64_t *>(c->counter.p), nullptr, 0,
@@ -329,8 +356,11 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     double2 *B = static_cast<double2 *>(c->vB.p);
     hipError_t e = hipSuccess;
 
-    // pipelined steps sum the norms of the check themselves
-    const bool pipe = use_pipe(*c, flags, keep && adj_step_ends(c, 0)) && ((flags & CHEBTD_GRAPH) == 0 || keep);
+    // the one-workgroup chain kernel keeps psi_s but not the step-end pairs
+    const bool small = c->kind == HKind::Chain && chain_small_fits(c->n) &&
+                       !(flags & CHEBTD_NO_PERSISTENT) && !(keep && adj_step_ends(c, 0));
+    // pipelined and tiled steps sum the norms of the check themselves
+    const bool pipe = !small && use_pipe(*c, flags, keep && adj_step_ends(c, 0)) && ((flags & CHEBTD_GRAPH) == 0 || keep);
     if (check && !pipe) {
         e = enqueue_norm(c, s, P, 0);
         if (e != hipSuccess) return hip_fail(c, e, "initial norm");
@@ -340,9 +370,6 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
         if (e != hipSuccess) return hip_fail(c, e, "counter reset");
     }
 
-    // the one-workgroup chain kernel keeps psi_s but not the step-end pairs
-    const bool small = c->kind == HKind::Chain && chain_small_fits(c->n) &&
-                       !(flags & CHEBTD_NO_PERSISTENT) && !(keep && adj_step_ends(c, 0));
     if (small) {
         e = launch_chain_small(*c, s, P, P, static_cast<const double2 *>(c->gamma_dev.p), K, norm_dev,
                                energy_dev, keep ? adj_checkpoint(c, 0, K) : nullptr);
@@ -360,8 +387,8 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
         }
         if (K & 1) {
             if (use_pipe(*c, flags, false)) {
-                double *sums = static_cast<double *>(c->pipe_sums.p);
-                e = enqueue_step_pipe(c, s, P, B, nullptr, sums, nullptr);
+                double *sums = c->pipe_sums;
+                e = enqueue_step_pipe(c, s, P, B, nullptr, nullptr, sums, nullptr);
                 if (e == hipSuccess && (norm_dev || energy_dev))
                     e = launch_ne_steps(s, {sums, c->pipe_part, (int)(c->pipe_part / 2), 1, c->a, c->b, norm_dev,
                                             energy_dev, K - 1, nullptr, nullptr, 0, nullptr, 0});
