@@ -260,8 +260,8 @@ bool chain_small_fits(int64_t n);
 // The same run over several workgroups (chain.hip): R sites per thread, T
 // threads, H halo sites per side (orders between exchanges), S own sites per
 // workgroup (R T = S + 2 H), P workgroups; R = 0 when one workgroup runs it.
-constexpr int kChainRing = 128;  // steps of norm/energy partials in flight (>= P + 1)
-constexpr int kChainMaxWG = 64;  // most workgroups of one run
+constexpr int kChainRing = 256;   // most steps of one launch
+constexpr int kChainMaxWG = 128;  // most workgroups of one run
 struct ChainMultiCfg {
     int R = 0, T = 0, H = 0;
     int64_t S = 0, P = 0;
@@ -270,9 +270,9 @@ ChainMultiCfg chain_multi_config(int64_t n);
 size_t chain_multi_scratch_bytes(const ChainMultiCfg &cfg);
 // device address of that run's timeout flag (int32) when it runs for c, else null
 int32_t *chain_multi_timeout(const Ctx &c);
-hipError_t launch_chain_small(const Ctx &c, hipStream_t s, double2 *psi, double2 *out,
-                              const double2 *gamma_dev, int64_t K, double *norm_out,
-                              double *energy_out, double2 *ckpt);
+// check (host-visible, or null): as NeSteps::check; *checked: it was filled
+hipError_t launch_chain_small(const Ctx &c, hipStream_t s, double2 *psi, double2 *out, int64_t K, double *norm_out,
+                              double *energy_out, double2 *ckpt, double *check, bool *checked);
 hipError_t launch_fill_zero(hipStream_t s, double *p, int64_t count);
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,
                             int64_t nnz, int64_t *flag);

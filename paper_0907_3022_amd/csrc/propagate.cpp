@@ -361,18 +361,21 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
                        !(flags & CHEBTD_NO_PERSISTENT) && !(keep && adj_step_ends(c, 0));
     // pipelined and tiled steps sum the norms of the check themselves
     const bool pipe = !small && use_pipe(*c, flags, keep && adj_step_ends(c, 0)) && ((flags & CHEBTD_GRAPH) == 0 || keep);
-    if (check && !pipe) {
+    // the several-workgroup chain run as well
+    const bool chain_sums = small && chain_multi_timeout(*c);
+    bool checked = pipe;
+    if (check && !pipe && !chain_sums) {
         e = enqueue_norm(c, s, P, 0);
         if (e != hipSuccess) return hip_fail(c, e, "initial norm");
     }
-    if ((norm_dev || energy_dev) && !pipe) {
+    if ((norm_dev || energy_dev) && !pipe && !small) {
         e = launch_reset_counter(s, static_cast<int64_t *>(c->counter.p));
         if (e != hipSuccess) return hip_fail(c, e, "counter reset");
     }
 
     if (small) {
-        e = launch_chain_small(*c, s, P, P, static_cast<const double2 *>(c->gamma_dev.p), K, norm_dev,
-                               energy_dev, keep ? adj_checkpoint(c, 0, K) : nullptr);
+        e = launch_chain_small(*c, s, P, P, K, norm_dev, energy_dev, keep ? adj_checkpoint(c, 0, K) : nullptr,
+                               check ? c->pinned : nullptr, &checked);
         if (e != hipSuccess) return hip_fail(c, e, "persistent chain kernel");
     } else if (pipe) {
         e = run_pipe(c, s, P, K, keep, nullptr, 0, norm_dev, energy_dev, check ? c->pinned : nullptr);
@@ -413,7 +416,7 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     }
 
     if (!check) return CHEBTD_OK;
-    if (!pipe) {
+    if (!checked) {
         e = enqueue_norm(c, s, P, 2);
         if (e == hipSuccess)
             e = hipMemcpyAsync(c->pinned, c->results.p, 4 * sizeof(double), hipMemcpyDeviceToHost, s);

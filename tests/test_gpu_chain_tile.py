@@ -56,3 +56,25 @@ def test_tiled_graph_and_driven_steps(torch, cheb):
     ctx.propagate_td(psi, V)
     np.testing.assert_array_equal(psi.cpu().numpy(), p1)
     ctx.close()
+
+
+# the whole-run kernels take at most 256 steps a launch: a longer run equals
+# the same run in parts, its norms, energies and end-of-call check included
+@pytest.mark.parametrize("n", [129, 300, 1000])
+def test_chain_run_longer_than_a_launch(torch, cheb, n):
+    case = chain_case(n, state="dense")
+    K = 600
+    say(f"[gpu] chain run of {K} steps n={n}")
+    ctx, p1, n1, e1, plan = run(torch, cheb, case, 0.001, K)
+    psi = torch.from_numpy(case["psi0"].copy()).cuda()
+    nrm = torch.zeros(K, dtype=torch.float64, device="cuda")
+    en = torch.zeros_like(nrm)
+    for a in (0, 200, 400):
+        ctx.propagate(psi, 200, nrm[a:a + 200], en[a:a + 200])
+    ctx.close()
+    np.testing.assert_array_equal(psi.cpu().numpy(), p1)
+    np.testing.assert_array_equal(nrm.cpu().numpy(), n1)
+    np.testing.assert_array_equal(en.cpu().numpy(), e1)
+    ref, rn, re = O.propagate(case["H"], plan, case["psi0"], K, want_obs=True)
+    assert_state_close(p1, ref)
+    np.testing.assert_allclose(n1, rn, rtol=1e-11)
