@@ -13,6 +13,7 @@
 #include "chain_tile.h"
 #include "pair.h"
 #include "pipe.h"
+#include "ribbon_tile.h"
 
 using namespace chebtd;
 
@@ -528,10 +529,21 @@ static int plan_common(Ctx *c, double dt, int M)
     // pass
     c->pipe = plan_pipe(*c, M);
     c->tile = plan_tile(*c, M);
+    if (c->kind == HKind::Honeycomb) {
+        double us;
+        c->tile = plan_ribbon_tile(c->W, c->L, c->edge, M, c->num_cus, &us);
+        if (!c->pipe.empty() && !std::getenv("CHEBTD_TILE") &&
+            pipe_time(c->W, c->L, c->pipe, c->num_cus) < us)
+            c->tile.R = 0;
+    }
     size_t sums = 0;
     if (!c->pipe.empty() || c->tile.R) {
-        const int64_t nb = c->tile.R ? tile_blocks(*c, c->tile.R, c->tile.depths.front()) : pipe_blocks(*c, c->pipe.front());
-        const int64_t nl = c->tile.R ? tile_blocks(*c, c->tile.R, c->tile.depths.back()) : pipe_blocks(*c, c->pipe.back());
+        auto blocks = [&](bool last) -> int64_t {
+            if (!c->tile.R) return pipe_blocks(*c, last ? c->pipe.back() : c->pipe.front());
+            const int D = last ? c->tile.depths.back() : c->tile.depths.front();
+            return c->kind == HKind::Chain ? tile_blocks(*c, c->tile.R, D) : ribbon_tile_blocks(c->L, D);
+        };
+        const int64_t nb = blocks(false), nl = blocks(true);
         c->pipe_last = (int)nl;
         c->pipe_part = 2 * nb;
         c->pipe_ring = (int)std::max<int64_t>(2, std::min<int64_t>(32, (int64_t(4) << 20) / (16 * nb)));

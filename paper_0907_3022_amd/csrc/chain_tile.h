@@ -31,7 +31,8 @@ struct TileArgs {
 
 constexpr int kTilePad = 12;  // weights read past M
 
-// R sites per lane; orders per pass, in launch order; empty: no tiled passes
+// chains: R sites per lane; orders per pass, in launch order; empty: no tiled
+// passes
 TilePlan plan_tile(const Ctx &c, int M);
 int64_t tile_blocks(const Ctx &c, int R, int D);
 hipError_t launch_tile(const Ctx &c, hipStream_t s, int R, const TileArgs &A, double *partials, double *knorm);

@@ -56,6 +56,8 @@ struct PipeArgs {
 
 // passes of a step of M orders (the last one padded), empty: not pipelined
 std::vector<PipeShape> plan_pipe(const Ctx &c, int M);
+// their estimated time, us
+double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int num_cus);
 // the same without the chunks, for lattices of `sites` sites in all
 std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M);
 // iterations of the longest walk when W rows are cut into n chunks

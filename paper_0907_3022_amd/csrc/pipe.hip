@@ -108,6 +108,12 @@ int32_t pipe_iterations(int DW, int NW, int32_t W, int32_t n)
 // 0.74 us for two together (zigzag, five orders per wavefront: 128 x 8192 in
 // 2 / 3 / 5 chunks 52.8 / 63.5 / 55.5 us a step, 1024 x 32768 in 1 / 2 / 4 / 8
 // chunks 789 / 700 / 687 / 763 us).  CHEBTD_PIPE_CHUNKS overrides.
+static double pipe_rounds(int64_t wgs, int NW, int num_cus)
+{
+    const int64_t slots = (int64_t)num_cus * (NW <= 4 ? 2 : 1), rest = wgs % slots;
+    return (double)(wgs / slots) + (rest == 0 ? 0.0 : rest <= num_cus && NW <= 4 ? 0.6 : 1.0);
+}
+
 static int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
 {
     const int D = DW * NW;
@@ -120,16 +126,24 @@ static int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
     double bt = 1e300;
     const int64_t limit = std::min(most, std::max<int64_t>(1, 4 * slots / strips));
     for (int64_t n = 1; n <= limit; ++n) {
-        const int64_t wgs = strips * n, rest = wgs % slots;
-        const double alone = NW <= 4 ? 0.6 : 1.0;
-        const double rounds = (double)(wgs / slots) + (rest == 0 ? 0.0 : rest <= num_cus ? alone : 1.0);
-        const double t = rounds * pipe_iterations(DW, NW, (int32_t)W, (int32_t)n);
+        const double t = pipe_rounds(strips * n, NW, num_cus) * pipe_iterations(DW, NW, (int32_t)W, (int32_t)n);
         if (t < bt) {
             bt = t;
             best = n;
         }
     }
     return (int)best;
+}
+
+// An iteration of two workgroups on a CU (one of eight wavefronts): 0.74 us
+// at five orders per wavefront, less in proportion below.
+double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int num_cus)
+{
+    double us = 0.0;
+    for (const PipeShape &p : passes)
+        us += 3.0 + pipe_rounds(ceil_div(L, pipe_strip_cols(p.depth())) * p.chunks, p.NW, num_cus) *
+                        pipe_iterations(p.DW, p.NW, (int32_t)W, p.chunks) * (p.NW <= 4 ? 0.14 + 0.12 * p.DW : 0.55);
+    return us;
 }
 
 // Passes of a step of M orders, the last padded with orders of weight 0: the

@@ -13,6 +13,7 @@
 #include "chain_tile.h"
 #include "pair.h"
 #include "pipe.h"
+#include "ribbon_tile.h"
 
 namespace chebtd {
 int fail(Ctx *c, int code, const std::string &msg);
@@ -164,7 +165,8 @@ hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, 
         A.r = c->rweight_dev + k;
         A.D = c->tile.depths[i];
         A.k0 = k;
-        hipError_t e = launch_tile(*c, s, c->tile.R, A, partials, last ? knorm : nullptr);
+        hipError_t e = c->kind == HKind::Chain ? launch_tile(*c, s, c->tile.R, A, partials, last ? knorm : nullptr)
+                                               : launch_ribbon_tile(*c, s, A, partials, last ? knorm : nullptr);
         if (e != hipSuccess) return e;
         X = A.out1;
         Y = A.out2;
