@@ -223,9 +223,9 @@ int chebtd_create(chebtd_ctx **out, void *hip_stream)
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess)
         e = hipDeviceGetAttribute(&c->num_cus, hipDeviceAttributeMultiprocessorCount, c->device);
-    if (e == hipSuccess) e = hipMalloc(&c->results.p, 16 * sizeof(double));
+    if (e == hipSuccess) e = hipMalloc(&c->results.p, 16 * sizeof(double) + kStepSumBytes);
     if (e == hipSuccess) {
-        c->results.bytes = 16 * sizeof(double);
+        c->results.bytes = 16 * sizeof(double) + kStepSumBytes;
         e = hipMalloc(&c->counter.p, 4 * sizeof(int64_t));
     }
     if (e == hipSuccess) {
@@ -524,9 +524,9 @@ static int plan_common(Ctx *c, double dt, int M)
     hipError_t e = hipMemcpy(c->gamma_dev.p, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_plan upload");
     const size_t vbytes = (size_t)c->n * 2 * sizeof(double);
-    // pipelined or tiled steps: behind vB the head partials of up to 32 steps
-    // (4 MiB at most, or two steps), then a norm partial per block of the last
-    // pass
+    // pipelined or tiled steps: the head partials of up to 32 steps, then a
+    // norm partial per block of the last pass, in the context's step sums, or
+    // for lattices of very many blocks two steps' behind vB
     c->pipe = plan_pipe(*c, M);
     c->tile = plan_tile(*c, M);
     if (c->kind == HKind::Honeycomb) {
@@ -546,12 +546,17 @@ static int plan_common(Ctx *c, double dt, int M)
         const int64_t nb = blocks(false), nl = blocks(true);
         c->pipe_last = (int)nl;
         c->pipe_part = 2 * nb;
-        c->pipe_ring = (int)std::max<int64_t>(2, std::min<int64_t>(32, (int64_t(4) << 20) / (16 * nb)));
-        sums = ((size_t)c->pipe_ring * (size_t)c->pipe_part + (size_t)nl) * sizeof(double);
+        const int64_t fit = ((int64_t)(kStepSumBytes / sizeof(double)) - nl) / c->pipe_part;
+        c->pipe_ring = (int)std::min<int64_t>(32, fit);
+        if (c->pipe_ring < 2) {
+            c->pipe_ring = 2;
+            sums = (size_t)(2 * c->pipe_part + nl) * sizeof(double);
+        }
     }
     if ((rc = ensure(c, c->vA, vbytes, "work vector A")) || (rc = ensure(c, c->vB, vbytes + sums, "work vector B")))
         return rc;
-    c->pipe_sums = reinterpret_cast<double *>(static_cast<char *>(c->vB.p) + vbytes);
+    c->pipe_sums = sums ? reinterpret_cast<double *>(static_cast<char *>(c->vB.p) + vbytes)
+                        : static_cast<double *>(c->results.p) + 16;
     // two more vectors let brick-wall Hamiltonians advance two orders per pass
     c->use_pairs = false;
     c->passes.clear();

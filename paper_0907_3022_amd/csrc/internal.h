@@ -160,10 +160,10 @@ struct Ctx {
     int pipe_ring = 0;       // steps whose head partials are in flight
     int64_t pipe_part = 0;   // doubles per step of them
     int pipe_last = 0;       // blocks of a step's last pass
-    double *pipe_sums = nullptr;  // [pipe_ring][pipe_part], then the last pass's norm partials (behind vB)
+    double *pipe_sums = nullptr;  // [pipe_ring][pipe_part], then the last pass's norm partials
     // reduction scratch: partial sums, step counter, results
     DevBuf partials;   // double[2 * max_blocks]
-    DevBuf results;    // double[16]
+    DevBuf results;    // double[16], then kStepSumBytes of per-step partial sums
     DevBuf counter;    // int64[4]
     DevBuf chainx;     // exchange strips, flags and partials of the several-workgroup chain run
     double *pinned = nullptr;  // host pinned double[16]
@@ -214,6 +214,7 @@ int holstein_build(int L, int nph, double t, double w0, const double *g, const d
 // Kernel launchers (kernels.hip).  All enqueue on `s` and return hipError_t.
 // ---------------------------------------------------------------------------
 constexpr int kBlock = 256;
+constexpr size_t kStepSumBytes = size_t(1) << 20;
 // LDS the Holstein walk may give its binomial table (beyond it, the walk
 // reads the per-state partner tables instead)
 constexpr int kHolBinomBytes = 16384;
