@@ -691,13 +691,20 @@ int64_t grid_blocks(const Ctx &c)
     return (c.n + kBlock - 1) / kBlock;
 }
 
-// Electron sites per thread of the Holstein walk (measured on MI355X with the
-// XCD-contiguous order and acc every third order): all of them (L = 10 ring:
-// 23.2 us per order against 24.4 for groups of five; L = 18 polaron: 10.60 ms
-// against 10.82 for groups of nine and 10.88 for six); hol_spt > 0 groups them
+// Electron sites per thread of the Holstein walk.  A walk over all sites reads
+// each v_k value once, but needs enough configurations to fill the chip; with
+// one or two sites per thread v_k is read up to three times, from the caches.
+// Measured on MI355X, us per order with 1 / 2 / 5 / all sites: 3.8 / 4.8 / 7.7
+// / 9.0 at 10296 states (L = 6), 4.6 / 5.3 / 8.2 / 11.7 at 102960 (8), 7.2 /
+// 7.7 / 10.8 / 15.1 at 437580 (9), 8.8 / 8.4 / 12.3 / 20.5 at 604656 (12), 14.1
+// / 12.7 / 13.2 / 19.1 at 923780 (10), 27.1 / 24.7 / 24.2 / 23.3 at 1.85M (10),
+// 55 / 55 / 61 / 43 at 3.9M (11); the L = 18 polaron 10.60 ms with all against
+// 10.82 for groups of nine.  hol_spt > 0 groups them
 static int hol_sites_per_thread(const Ctx &c)
 {
-    return c.hol_spt > 0 ? (int)std::min<int64_t>(c.hol_spt, c.hol_L) : (int)c.hol_L;
+    if (c.hol_spt > 0) return (int)std::min<int64_t>(c.hol_spt, c.hol_L);
+    const int want = c.n <= 500000 ? 1 : c.n <= 1400000 ? 2 : c.hol_L;
+    return std::min(want, c.hol_L);
 }
 
 static int64_t hol_walk_blocks(const Ctx &c)
