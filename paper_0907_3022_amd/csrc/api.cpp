@@ -527,7 +527,10 @@ static int plan_common(Ctx *c, double dt, int M)
     // pipelined or tiled steps: the head partials of up to 32 steps, then a
     // norm partial per block of the last pass, in the context's step sums, or
     // for lattices of very many blocks two steps' behind vB
-    c->pipe = plan_pipe(*c, M);
+    c->pipe = plan_pipe(*c, M, false);
+    static const int rest_of[4] = {0, 5, 2, 3};  // pipelined depths are multiples of four
+    c->pipe_rest = rest_of[M & 3];
+    c->pipe_ends = M - c->pipe_rest >= 8 ? plan_pipe(*c, M - c->pipe_rest, true) : std::vector<PipeShape>();
     c->tile = plan_tile(*c, M);
     if (c->kind == HKind::Honeycomb) {
         double us;
@@ -539,12 +542,17 @@ static int plan_common(Ctx *c, double dt, int M)
     size_t sums = 0;
     if (!c->pipe.empty() || c->tile.R) {
         auto blocks = [&](bool last) -> int64_t {
-            if (!c->tile.R) return pipe_blocks(*c, last ? c->pipe.back() : c->pipe.front());
+            if (!c->tile.R) {
+                // either plan's first (last) pass
+                int64_t nb = pipe_blocks(*c, last ? c->pipe.back() : c->pipe.front());
+                if (!c->pipe_ends.empty())
+                    nb = std::max(nb, pipe_blocks(*c, last ? c->pipe_ends.back() : c->pipe_ends.front()));
+                return nb;
+            }
             const int D = last ? c->tile.depths.back() : c->tile.depths.front();
             return c->kind == HKind::Chain ? tile_blocks(*c, c->tile.R, D) : ribbon_tile_blocks(c->L, D);
         };
         const int64_t nb = blocks(false), nl = blocks(true);
-        c->pipe_last = (int)nl;
         c->pipe_part = 2 * nb;
         const int64_t fit = ((int64_t)(kStepSumBytes / sizeof(double)) - nl) / c->pipe_part;
         c->pipe_ring = (int)std::min<int64_t>(32, fit);

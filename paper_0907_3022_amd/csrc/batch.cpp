@@ -129,7 +129,7 @@ static int build_pipe(Ctx *c, BatchState *b)
     std::vector<std::vector<PipeShape>> plan(ns);
     size_t maxpass = 0;
     for (int s = 0; s < ns; ++s) {
-        plan[s] = plan_pipe_shapes(total, b->M[s]);
+        plan[s] = plan_pipe_shapes(total, b->M[s], false);
         if (plan[s].empty()) return CHEBTD_OK;  // pipe_ok stays false
         maxpass = std::max(maxpass, plan[s].size());
     }

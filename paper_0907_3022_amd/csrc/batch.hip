@@ -270,7 +270,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_batch_pipe(const SysDev *__restr
     A.acc_in = nxt;
     A.acc_out = nxt;
     A.ckpt = nullptr;
-    A.fin = sd.phase;
+    A.fin = last ? sd.phase : make_double2(1.0, 0.0);
     A.r = rw + sd.rw_off + pb.k0;
     double s0 = 0.0, s1 = 0.0;
     if (sd.edge == CHEBTD_ZIGZAG)

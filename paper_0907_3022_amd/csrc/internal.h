@@ -156,10 +156,13 @@ struct Ctx {
     // pipelined passes of one step (pipe.h): ribbons of M >= 2, unless a depth
     // is forced; empty: the passes above run
     std::vector<PipeShape> pipe;
-    TilePlan tile;           // the same for chains
+    // the same for runs that keep each step's v_{M-1}, v_M: passes that add up
+    // to M - pipe_rest orders, the rest in one deep or two-order pass
+    std::vector<PipeShape> pipe_ends;
+    int pipe_rest = 0;
+    TilePlan tile;           // tiled passes of chains and narrow ribbons
     int pipe_ring = 0;       // steps whose head partials are in flight
     int64_t pipe_part = 0;   // doubles per step of them
-    int pipe_last = 0;       // blocks of a step's last pass
     double *pipe_sums = nullptr;  // [pipe_ring][pipe_part], then the last pass's norm partials
     // reduction scratch: partial sums, step counter, results
     DevBuf partials;   // double[2 * max_blocks]

@@ -50,16 +50,17 @@ struct PipeArgs {
     const double2 *acc_in;     // head: not read
     double2 *acc_out;
     double2 *ckpt;             // head: a copy of psi, or null
-    double2 fin;               // e^{-ib dt}
+    double2 fin;               // the step's last pass: e^{-ib dt}; else 1
     const double *r;           // r[j]: weight of order k0+j (r[0]: the head's); 0 past M
 };
 
-// passes of a step of M orders (the last one padded), empty: not pipelined
-std::vector<PipeShape> plan_pipe(const Ctx &c, int M);
+// passes of a step of M orders (the last one padded, or exact), empty: not
+// pipelined
+std::vector<PipeShape> plan_pipe(const Ctx &c, int M, bool exact);
 // their estimated time, us
 double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int num_cus);
 // the same without the chunks, for lattices of `sites` sites in all
-std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M);
+std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact);
 // iterations of the longest walk when W rows are cut into n chunks
 int32_t pipe_iterations(int DW, int NW, int32_t W, int32_t n);
 int64_t pipe_blocks(const Ctx &c, const PipeShape &s);

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pipe(PipeOp op, PipeArgs A, doub
             partials[2 * blockIdx.x + 1] = s1;
         }
     }
-    if (w == NW - 1 && A.out2 == nullptr && knorm) {
+    if (w == NW - 1 && knorm) {
         s0 = wave_sum(s0);
         if (lane == 0) knorm[blockIdx.x] = s0;
     }
@@ -151,10 +151,11 @@ double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int
 // and 3.4 10^7 sites (10 x 1000 armchair, 128 x 8192 and 1024 x 32768 zigzag).
 // Not pipelined: lattices past the 32-bit offsets (deep_offsets_fit), and a
 // depth forced by CHEBTD_DEPTH.  CHEBTD_PIPE=DW,NW forces one shape, 0 none.
-std::vector<PipeShape> plan_pipe(const Ctx &c, int M)
+// exact: no padding (the passes' orders add up to M, or there are none).
+std::vector<PipeShape> plan_pipe(const Ctx &c, int M, bool exact)
 {
     if (c.kind != HKind::Honeycomb || !deep_offsets_fit(c.W, c.L)) return {};
-    std::vector<PipeShape> out = plan_pipe_shapes(c.n, M);
+    std::vector<PipeShape> out = plan_pipe_shapes(c.n, M, exact);
     for (size_t i = 0; i < out.size(); ++i)
         out[i].chunks = i > 0 && out[i].DW == out[i - 1].DW && out[i].NW == out[i - 1].NW
                             ? out[i - 1].chunks
@@ -162,7 +163,7 @@ std::vector<PipeShape> plan_pipe(const Ctx &c, int M)
     return out;
 }
 
-std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M)
+std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact)
 {
     std::vector<PipeShape> out;
     if (M < 2 || std::getenv("CHEBTD_DEPTH")) return out;
@@ -181,7 +182,7 @@ std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M)
     for (int m = 1; m <= M; ++m)
         for (int q = 0; q < (int)(sizeof cands / sizeof cands[0]); ++q) {
             const Cand &x = cands[q];
-            if (fdw && (x.DW != fdw || x.NW != fnw)) continue;
+            if ((fdw && (x.DW != fdw || x.NW != fnw)) || (exact && x.DW * x.NW > m)) continue;
             const double t = best[(size_t)std::max(0, m - x.DW * x.NW)] +
                              (sites < (int64_t(1) << 17) ? x.tiny : sites < (int64_t(1) << 22) ? x.small : x.large);
             if (t < best[(size_t)m]) {

@@ -104,13 +104,13 @@ __device__ __forceinline__ void add_order(int l, double r, double2 v, double2 &P
 }
 
 // Wavefront w of the workgroup.  ROLE: kHead (a step's first pass; kHeadKeep
-// also copies psi) and kFirst read memory, kLast and kFinal (an inner pass, the
-// step's last) write it, kMid does neither.
+// also copies psi) and kFirst read memory, kLast (acc and the last two orders)
+// and kFinal (acc alone) write it, kMid does neither.
 template <int EDGE, int DW, int NW, int ROLE>
 __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w, int32_t strip, int32_t ys, int32_t ye,
                                      int32_t tend, PipeSlot (*slots)[2], double &s0, double &s1)
 {
-    constexpr bool FIRST = ROLE <= kFirst, HEAD = ROLE <= kHeadKeep, LASTW = ROLE >= kLast, FINAL = ROLE == kFinal;
+    constexpr bool FIRST = ROLE <= kFirst, HEAD = ROLE <= kHeadKeep, LASTW = ROLE >= kLast;
     constexpr int D = DW * NW, HL = pipe_halo_lanes(D), S = pipe_strip_cols(D);
     static_assert(DW >= 2 && DW <= 5 && NW >= 2 && D % 4 == 0 && D <= kMaxPipe, "depth");
     const int lane = threadIdx.x & 63;
@@ -284,12 +284,10 @@ __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w,
             for (int c = 0; c < 2; ++c) {
                 // the last wavefront's sum is turned by i^((NW - 1) DW)
                 const double2 p = turn<4 * NW - (NW - 1) * DW + 4 * DW * NW>(P[sR][c]);
-                double2 o = p;
-                if constexpr (FINAL) {
-                    o = make_double2(fma(A.fin.x, p.x, -(A.fin.y * p.y)), fma(A.fin.x, p.y, A.fin.y * p.x));
-                    const double m = __longlong_as_double(ok ? 0x3FF0000000000000ll : 0ll);
-                    s0 = fma(m, fma(o.y, o.y, o.x * o.x), s0);
-                }
+                const double2 o =
+                    make_double2(fma(A.fin.x, p.x, -(A.fin.y * p.y)), fma(A.fin.x, p.y, A.fin.y * p.x));
+                const double m = __longlong_as_double(ok ? 0x3FF0000000000000ll : 0ll);
+                s0 = fma(m, fma(o.y, o.y, o.x * o.x), s0);
                 st2(A.acc_out, R, ok, s16[c], o);
             }
         } else {
@@ -323,8 +321,8 @@ __device__ __forceinline__ int pipe_wave()
 }
 
 // The workgroup's share: strip `strip`, rows [ys, ye).  sums: <v0|v0> and
-// <v0|H~ v0> of a head pass (wavefront 0's lanes), sum |acc|^2 of a step's
-// last pass (the last wavefront's).
+// <v0|H~ v0> of a head pass (wavefront 0's lanes), sum |acc|^2 (the last
+// wavefront's).
 template <int EDGE, int DW, int NW>
 __device__ __forceinline__ void pipe_block(const PipeOp &op, const PipeArgs &A, int32_t strip, int32_t ys, int32_t ye,
                                            PipeSlot (*slots)[2], double &s0, double &s1)

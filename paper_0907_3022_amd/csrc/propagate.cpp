@@ -132,18 +132,28 @@ hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt,
     return k == c->M ? hipSuccess : hipErrorInvalidValue;
 }
 
-// Whether the steps run as pipelined (ribbons) or tiled (chains) passes.
-// ends: the step-end pairs are wanted, which a padded last pipelined pass does
-// not form.
+// Whether the steps run as pipelined or tiled passes.  ends: the step-end
+// pairs are wanted, which a padded last pipelined pass does not form.
 bool use_pipe(const Ctx &c, unsigned flags, bool ends)
 {
-    return (c.tile.R || (!c.pipe.empty() && !ends)) && !(flags & CHEBTD_SINGLE_ORDER);
+    return (c.tile.R || !(ends ? c.pipe_ends : c.pipe).empty()) && !(flags & CHEBTD_SINGLE_ORDER);
+}
+
+// Blocks of the first (last) pass of such a step.
+int step_blocks(const Ctx &c, bool ends, bool last)
+{
+    if (c.tile.R) {
+        const int D = last ? c.tile.depths.back() : c.tile.depths.front();
+        return (int)(c.kind == HKind::Chain ? tile_blocks(c, c.tile.R, D) : ribbon_tile_blocks(c.L, D));
+    }
+    const std::vector<PipeShape> &p = ends ? c.pipe_ends : c.pipe;
+    return (int)pipe_blocks(c, last ? p.back() : p.front());
 }
 
 // One time step cur -> nxt in pipelined passes; partials: the head's norm and
 // energy partials, knorm: the last pass's norm partials (or null).  Pass
 // outputs alternate between (vA, vC) and (vD, cur), as above.
-// ends (or null; chains): 2 n values that receive v_{M-1}, v_M.
+// ends (or null): 2 n values that receive v_{M-1}, v_M.
 hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double2 *ends,
                              double *partials, double *knorm)
 {
@@ -173,27 +183,38 @@ hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, 
         k += A.D;
     }
     if (c->tile.R) return k == c->M ? hipSuccess : hipErrorInvalidValue;
-    if (ends) return hipErrorInvalidValue;
-    for (size_t i = 0; i < c->pipe.size(); ++i) {
-        const PipeShape &sh = c->pipe[i];
-        const bool last = i + 1 == c->pipe.size();
+    const std::vector<PipeShape> &passes = ends ? c->pipe_ends : c->pipe;
+    const int rest = ends ? c->pipe_rest : 0;
+    for (size_t i = 0; i < passes.size(); ++i) {
+        const PipeShape &sh = passes[i];
+        const bool last = i + 1 == passes.size(), end = last && !rest;
         PipeArgs A{};
         A.vkm1 = X;
         A.vk = Y;
-        A.out1 = last ? nullptr : out[i & 1][0];
-        A.out2 = last ? nullptr : out[i & 1][1];
+        A.out1 = !end ? out[i & 1][0] : ends;
+        A.out2 = !end ? out[i & 1][1] : ends ? ends + c->n : nullptr;
         A.acc_in = nxt;
         A.acc_out = nxt;
         A.ckpt = i == 0 ? ckpt : nullptr;
-        A.fin = c->phase;
+        A.fin = last ? c->phase : make_double2(1.0, 0.0);
         A.r = c->rweight_dev + k;
-        hipError_t e = launch_pipe(*c, s, sh, A, partials, last ? knorm : nullptr);
+        hipError_t e = launch_pipe(*c, s, sh, A, partials, end ? knorm : nullptr);
         if (e != hipSuccess) return e;
         X = A.out1;
         Y = A.out2;
         k += sh.depth();
     }
-    return k >= c->M ? hipSuccess : hipErrorInvalidValue;
+    if (rest) {
+        double2 g[kMaxDepth + 1] = {};
+        for (int j = 1; j <= rest; ++j) g[j] = weight(c, k + j);
+        hipError_t e = rest == 2 ? launch_pair(*c, s, c->pair_rows, false, X, Y, ends, ends + c->n, nxt, g[0], g[1],
+                                               g[2], nullptr, nullptr, nullptr)
+                                 : launch_deep(*c, s, rest, c->deep_rows[rest], false, X, Y, ends, ends + c->n, nxt, g,
+                                               nullptr, nullptr, nullptr);
+        if (e != hipSuccess) return e;
+        k += rest;
+    }
+    return ends ? (k == c->M ? hipSuccess : hipErrorInvalidValue) : k >= c->M ? hipSuccess : hipErrorInvalidValue;
 }
 
 // K pipelined steps from P, alternating with vB.  norm and energy of the
@@ -210,6 +231,8 @@ hipError_t run_pipe(Ctx *c, hipStream_t s, double2 *P, int64_t K, bool keep, con
     const double *saved = *site;
     hipError_t e = hipSuccess;
     int64_t first = 0;
+    const bool ends = keep && adj_step_ends(c, 0);
+    const int nhead = step_blocks(*c, ends, false), nlast = step_blocks(*c, ends, true);
     for (int64_t st = 0; st < K && e == hipSuccess; ++st) {
         if (onsite) *site = onsite + st * stride;
         const int64_t slot = st - first;
@@ -219,9 +242,8 @@ hipError_t run_pipe(Ctx *c, hipStream_t s, double2 *P, int64_t K, bool keep, con
                               last && check ? knorm : nullptr);
         const bool wanted = norm_out || energy_out || (check && (first == 0 || last));
         if (e == hipSuccess && (last || slot + 1 == c->pipe_ring)) {
-            const NeSteps f{sums, c->pipe_part, (int)(c->pipe_part / 2), (int)(slot + 1), c->a, c->b, norm_out,
-                            energy_out, first, nullptr, last && check ? knorm : nullptr,
-                            c->pipe_last, check, first == 0};
+            const NeSteps f{sums, c->pipe_part, nhead, (int)(slot + 1), c->a, c->b, norm_out, energy_out, first,
+                            nullptr, last && check ? knorm : nullptr, nlast, check, first == 0};
             if (wanted) e = launch_ne_steps(s, f);
             first = st + 1;
         }
@@ -308,7 +330,7 @@ int get_pair_graph(Ctx *c, double2 *psi, double *norm_out, double *energy_out, u
         e1 = enqueue_step_pipe(c, c->cap_stream, psi, B, nullptr, nullptr, sums, nullptr);
         e2 = e1 == hipSuccess ? enqueue_step_pipe(c, c->cap_stream, B, psi, nullptr, nullptr, sums + c->pipe_part, nullptr) : e1;
         if (e2 == hipSuccess && (norm_out || energy_out))
-            e2 = launch_ne_steps(c->cap_stream, {sums, c->pipe_part, (int)(c->pipe_part / 2), 2, c->a, c->b, norm_out,
+            e2 = launch_ne_steps(c->cap_stream, {sums, c->pipe_part, step_blocks(*c, false, false), 2, c->a, c->b, norm_out,
                                                  energy_out, 0, static_cast<int64_t *>(c->counter.p), nullptr, 0,
                                                  nullptr, 0});
     } else {
@@ -365,8 +387,10 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     const bool pipe = !small && use_pipe(*c, flags, keep && adj_step_ends(c, 0)) && ((flags & CHEBTD_GRAPH) == 0 || keep);
     // the several-workgroup chain run as well
     const bool chain_sums = small && chain_multi_timeout(*c);
-    bool checked = pipe;
-    if (check && !pipe && !chain_sums) {
+    // (a step-end pass of the rest of the orders does not sum the last norm)
+    const bool pipe_sums = pipe && !(keep && adj_step_ends(c, 0) && !c->tile.R && c->pipe_rest);
+    bool checked = pipe_sums;
+    if (check && !pipe_sums && !chain_sums) {
         e = enqueue_norm(c, s, P, 0);
         if (e != hipSuccess) return hip_fail(c, e, "initial norm");
     }
@@ -380,7 +404,8 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
                                check ? c->pinned : nullptr, &checked);
         if (e != hipSuccess) return hip_fail(c, e, "persistent chain kernel");
     } else if (pipe) {
-        e = run_pipe(c, s, P, K, keep, nullptr, 0, norm_dev, energy_dev, check ? c->pinned : nullptr);
+        e = run_pipe(c, s, P, K, keep, nullptr, 0, norm_dev, energy_dev,
+                     check && pipe_sums ? c->pinned : nullptr);
         if (e != hipSuccess) return hip_fail(c, e, "pipelined steps");
     } else if ((flags & CHEBTD_GRAPH) && !keep) {
         hipGraphExec_t ge = nullptr;
@@ -395,7 +420,7 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
                 double *sums = c->pipe_sums;
                 e = enqueue_step_pipe(c, s, P, B, nullptr, nullptr, sums, nullptr);
                 if (e == hipSuccess && (norm_dev || energy_dev))
-                    e = launch_ne_steps(s, {sums, c->pipe_part, (int)(c->pipe_part / 2), 1, c->a, c->b, norm_dev,
+                    e = launch_ne_steps(s, {sums, c->pipe_part, step_blocks(*c, false, false), 1, c->a, c->b, norm_dev,
                                             energy_dev, K - 1, nullptr, nullptr, 0, nullptr, 0});
             } else {
                 e = enqueue_step(c, s, P, B, nullptr, nullptr, norm_dev, energy_dev, flags);

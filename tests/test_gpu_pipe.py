@@ -87,3 +87,24 @@ def test_pipelined_checkpoints_and_graph(torch, cheb):
                                  case["psi0"], mask, (lo, hi), 1.0, 3, cheb.ADJ_STEP)
     _, gr, ur = O.adjoint(H, O.Plan(lo, hi, 1.0), case["psi0"], 3, mask)
     assert rel_l2(g, gr) <= 1e-8 and rel_l2(u0, ur) <= 1e-10
+
+
+# the step-end pairs v_{M-1}, v_M of a checkpointing run come from exact
+# pipelined passes and, where M is no multiple of four, one pass of the rest:
+# every remainder, one and several passes, through the downward adjoint
+@pytest.mark.parametrize("dt", [0.42, 0.46, 0.5, 0.55, 1.0, 1.07, 1.14, 1.2, 4.0])
+def test_pipelined_step_ends(torch, cheb, dt):
+    import workloads as W
+    from test_gpu_adjoint import assert_grad_close, gpu_adjoint
+    w, l, edge = 50, 130, "zigzag"
+    case = honey_case(w, l, edge, state="dense")
+    eps, _ = W.ribbon_inputs(w, l, 0.5, 0)
+    mask = W.random_weights(w * l, 3)
+    H = O.honeycomb(w, l, eps, edge=edge)
+    lo, hi = H.gershgorin()
+    _, g, u0, prop = gpu_adjoint(torch, cheb, "honeycomb", dict(width=w, length=l, edge=edge), eps, case["psi0"], mask,
+                                 (lo, hi), dt, 2, cheb.ADJ_REVERSE)
+    say(f"[gpu] pipelined step ends dt={dt} M={prop.M}")
+    _, gr, ur = O.adjoint(H, O.Plan(lo, hi, dt), case["psi0"], 2, mask)
+    assert_grad_close(g, gr)
+    assert_state_close(u0, ur)
