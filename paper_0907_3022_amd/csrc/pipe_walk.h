@@ -76,6 +76,12 @@ __device__ __forceinline__ void row_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The loads of these values come before this point.  Without it the compiler
+// moves LDS reads whose first use lies behind a branch past a row_barrier() in
+// front of that branch, where the next wavefront's stores may overtake them.
+__device__ __forceinline__ void arrived(double2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void arrived(double (&v)[2]) { asm volatile("" : "+v"(v[0]), "+v"(v[1])); }
+
 constexpr int kHead = 0, kHeadKeep = 1, kFirst = 2, kMid = 3, kLast = 4, kFinal = 5;
 
 struct RowSet {
@@ -205,6 +211,13 @@ __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w,
     } else {
         for (int32_t t = 0; t + 1 < sp.t0; ++t) row_barrier();
         fetch(set[0], rd[1]);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            arrived(set[0].a[c]);
+            arrived(set[0].k[c]);
+            arrived(set[0].p[c]);
+        }
+        arrived(set[0].e);
         row_barrier();
     }
 
