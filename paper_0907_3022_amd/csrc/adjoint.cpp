@@ -15,6 +15,7 @@
 
 #include "internal.h"
 #include "pair.h"
+#include "pipe_rev.h"
 
 namespace chebtd {
 int fail(Ctx *c, int code, const std::string &msg);
@@ -42,6 +43,7 @@ struct AdjState {
     // pass above regenerated)
     bool down = false;
     std::vector<int> rdepths, cpslot;
+    int rev_chunks = 1;  // row chunks of the pipelined reverse passes
     DevBuf hpart;  // norm partials of the recomputation's head pass (unused)
 };
 
@@ -263,6 +265,23 @@ std::vector<int> rev_pass_depths(const Ctx &c)
     return depths;
 }
 
+// The same for the reverse mode: pipelined passes of kRevPipeDepth levels
+// first where the lattice takes them, the rest as above.
+std::vector<int> reverse_pass_depths(const Ctx &c)
+{
+    if (!rev_pipe_fits(c)) return rev_pass_depths(c);
+    const int D = kRevPipeDepth;
+    int n = c.M / D;
+    if (c.M - n * D == 1) --n;  // a pass of one level is none
+    std::vector<int> depths((size_t)std::max(n, 0), D);
+    Ctx rest;
+    rest.kind = c.kind;
+    rest.M = c.M - D * (int)depths.size();
+    const std::vector<int> tail = rev_pass_depths(rest);
+    depths.insert(depths.end(), tail.begin(), tail.end());
+    return depths;
+}
+
 // The sqrt mode's forward pass of one step on the downward path: from psi_s,
 // the passes of the downward sweep in reverse order (so every pass ends on
 // an order where a downward pass starts), each advancing its orders without
@@ -382,8 +401,24 @@ hipError_t reverse_sweep(Ctx *c, hipStream_t s, double2 *gbar_user, double *grad
                         p.vout2 = w;
                 }
             }
-            for (int j = 1; j <= d; ++j) p.cw[j - 1] = conj_weight(c, k - j + 1);
-            e = launch_rev_deep(*c, s, d, rev_rows(*c, d), p);
+            for (int j = 1; j <= d && j <= kMaxRevDepth; ++j) p.cw[j - 1] = conj_weight(c, k - j + 1);
+            if (d == kRevPipeDepth) {
+                RevPipeArgs A{p.uk2, p.uk1, p.v1, p.v0, p.out1, p.out2, p.vout1, p.vout2, p.gbar, p.grad};
+                // i^k e^{ib dt}
+                const double2 f = make_double2(c->phase.x, -c->phase.y);
+                switch (k & 3) {
+                    case 0: A.fac = f; break;
+                    case 1: A.fac = make_double2(-f.y, f.x); break;
+                    case 2: A.fac = make_double2(-f.x, -f.y); break;
+                    default: A.fac = make_double2(f.y, -f.x); break;
+                }
+                A.r = c->rweight_dev + k;
+                A.gf = 2.0 / c->a;
+                A.half = p.last0 ? 0.5 : 1.0;
+                e = launch_rev_pipe(*c, s, a->rev_chunks, A);
+            } else {
+                e = launch_rev_deep(*c, s, d, rev_rows(*c, d), p);
+            }
             if (e != hipSuccess) break;
             u.uk2 = o1;  // u_{k-d+2}
             u.uk1 = o2;  // u_{k-d+1}
@@ -429,7 +464,9 @@ int chebtd_reserve_adjoint(chebtd_ctx *ctx, int64_t max_steps, int mode)
     // the reverse mode, and the sqrt mode where the deep walk fits, sweep
     // downwards (M >= 2; M = 1 is level 0 alone)
     a->down = mode == CHEBTD_ADJ_REVERSE || (mode == CHEBTD_ADJ_SQRTM && rev_deep_fits(*c) && M >= 2);
-    a->rdepths = a->down ? rev_pass_depths(*c) : std::vector<int>();
+    a->rdepths = !a->down ? std::vector<int>()
+                 : mode == CHEBTD_ADJ_REVERSE ? reverse_pass_depths(*c) : rev_pass_depths(*c);
+    a->rev_chunks = a->down && rev_pipe_fits(*c) ? rev_pipe_chunks(*c) : 1;
     a->cpslot.assign(a->rdepths.size(), -1);
     int rc;
     if ((rc = ensure(c, a->ckpt, vb * (size_t)max_steps, "adjoint checkpoints"))) return rc;

@@ -61,6 +61,8 @@ std::vector<PipeShape> plan_pipe(const Ctx &c, int M, bool exact);
 double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int num_cus);
 // the same without the chunks, for lattices of `sites` sites in all
 std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact);
+// row chunks of a pass
+int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus);
 // iterations of the longest walk when W rows are cut into n chunks
 int32_t pipe_iterations(int DW, int NW, int32_t W, int32_t n);
 int64_t pipe_blocks(const Ctx &c, const PipeShape &s);

@@ -114,7 +114,7 @@ static double pipe_rounds(int64_t wgs, int NW, int num_cus)
     return (double)(wgs / slots) + (rest == 0 ? 0.0 : rest <= num_cus && NW <= 4 ? 0.6 : 1.0);
 }
 
-static int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
+int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
 {
     const int D = DW * NW;
     const int64_t most = std::max<int64_t>(1, (W - (D - 1)) / 8);  // at least 8 rows each

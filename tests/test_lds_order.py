@@ -12,7 +12,7 @@ import pytest
 from test_store_form import BUILD, disassemble
 
 # object, kernel, 128-bit LDS reads per row and wavefront
-KERNELS = [("pipe.hip", "k_pipe", 7), ("batch.hip", "k_batch_pipe", 7)]
+KERNELS = [("pipe.hip", "k_pipe", 7), ("batch.hip", "k_batch_pipe", 7), ("pipe_rev.hip", "k_rev_pipe", 12)]
 
 
 def reads_between_barriers(asm, kernel):
