@@ -194,8 +194,9 @@ std::vector<int> plan_passes(const Ctx &c, int M)
     return out;
 }
 
-void invalidate_h(Ctx *c)
+void invalidate_h(Ctx *c, bool csr = false)
 {
+    if (!csr) release(c->csr_buf);
     c->has_bounds = false;
     c->has_plan = false;
     c->holstein = false;
@@ -255,7 +256,7 @@ int chebtd_destroy(chebtd_ctx *ctx)
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     for (DevBuf *b : {&c->vA, &c->vB, &c->vC, &c->vD, &c->partials, &c->results, &c->counter, &c->gamma_dev,
                       &c->hol_occ, &c->hol_up, &c->hol_dn,
-                      &c->hol_tot, &c->hol_site, &c->hol_binom, &c->chainx})
+                      &c->hol_tot, &c->hol_site, &c->hol_binom, &c->chainx, &c->csr_buf})
         release(*b);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->ev_a) (void)hipEventDestroy(c->ev_a);
@@ -342,13 +343,26 @@ int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_
         return fail(c, CHEBTD_E_ARG,
                     "chebtd_h_csr: rowptr must run from 0 to nnz without decreasing and every column "
                     "must lie in [0, n)");
-    invalidate_h(c);
+    invalidate_h(c, true);
     c->kind = HKind::Csr;
     c->n = n;
     c->nnz = nnz;
     c->rowptr = rowptr_dev;
     c->col = col_dev;
     c->val = val_dev;
+    // Room for the copies of many-order calls (launch_csr_copy), if it is a
+    // small part of what is left on the device; without it the orders read
+    // the caller's arrays.
+    size_t left = 0, total = 0;
+    const size_t need = csr_copy_bytes(n, nnz);
+    if (c->csr_buf.bytes < need || c->csr_buf.bytes / 2 > need) release(c->csr_buf);
+    if (need && !c->csr_buf.p && hipMemGetInfo(&left, &total) == hipSuccess && need <= left / 8) {
+        if (hipMalloc(&c->csr_buf.p, need) == hipSuccess)
+            c->csr_buf.bytes = need;
+        else
+            c->csr_buf.p = nullptr;
+    }
+    (void)hipGetLastError();
     return ensure_partials(c);
 }
 

@@ -218,6 +218,50 @@ struct CsrRow {
         // (2/a) (H v - b v)
         return make_double2(op.s2 * fma(-op.b, vi.x, sx), op.s2 * fma(-op.b, vi.y, sy));
     }
+    // Where entry j of each row of a wavefront's 64 lies in the copy: behind
+    // all entries before j of the 64 rows, among the entries j of the rows
+    // that have one (`mask`), so that a load is contiguous without padding.
+    __device__ static __forceinline__ uint32_t copy_slot(uint64_t mask)
+    {
+        return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    }
+    // the same as apply2 from the copy of a real matrix: the sum in the same order
+    __device__ static __forceinline__ double2 apply2_real(const OpCsr &op, int64_t i, const double2 *v, double2 vi)
+    {
+        const int32_t p0 = op.rowptr32[i], len = op.rowptr32[i + 1] - p0;
+        const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane(p0);
+        double sx = 0.0, sy = 0.0;
+        uint32_t p = base;
+        for (int32_t j = 0; __ballot(len > j) != 0; j += 4) {
+            double h[4];
+            double2 x[4];
+            int32_t cc[4];
+            // rows that have ended read the 64 rows' first entry
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint64_t mask = __ballot(len > j + q);
+                const uint32_t at = len > j + q ? p + copy_slot(mask) : base;
+                h[q] = op.re[at];
+                cc[q] = op.col32[at];
+                p += (uint32_t)__popcll(mask);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = v[cc[q]];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double tx = fma(h[q], x[q].x, sx), ty = fma(h[q], x[q].y, sy);
+                sx = len > j + q ? tx : sx;
+                sy = len > j + q ? ty : sy;
+            }
+        }
+        return make_double2(op.s2 * fma(-op.b, vi.x, sx), op.s2 * fma(-op.b, vi.y, sy));
+    }
+    template <bool COPY>
+    __device__ static __forceinline__ double2 apply2_of(const OpCsr &op, int64_t i, const double2 *v, double2 vi)
+    {
+        if (COPY && *op.mixed == 0) return apply2_real(op, i, v, vi);
+        return apply2(op, i, v, vi);
+    }
 };
 
 // Matrix-free Holstein states (eq. (ghm)): state i = site * nconf + r.
@@ -295,6 +339,16 @@ inline OpCsr make_csr(const Ctx &c)
     op.rowptr = c.rowptr;
     op.col = c.col;
     op.val = reinterpret_cast<const double2 *>(c.val);
+    op.rowptr32 = op.col32 = nullptr;
+    op.re = nullptr;
+    op.mixed = nullptr;
+    if (c.csr_copy) {
+        char *p = static_cast<char *>(c.csr_buf.p);
+        op.mixed = reinterpret_cast<const int32_t *>(p);
+        op.re = reinterpret_cast<const double *>(p + 16);
+        op.col32 = reinterpret_cast<const int32_t *>(p + 16 + (size_t)c.nnz * 8);
+        op.rowptr32 = op.col32 + c.nnz;
+    }
     op.b = c.b;
     op.s2 = 2.0 / c.a;
     op.n = c.n;

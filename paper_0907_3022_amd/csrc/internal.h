@@ -72,6 +72,12 @@ struct OpCsr {
     const int64_t *rowptr;
     const int32_t *col;
     const double2 *val;
+    // a call's copy of a real matrix (k_csr_copy): 32-bit row starts, columns
+    // and real parts in the order the orders read them, and a word that is not
+    // 0 if an imaginary part is
+    const int32_t *rowptr32, *col32;
+    const double *re;
+    const int32_t *mixed;
     double b;
     double s2;  // 2/a
     int64_t n;
@@ -112,6 +118,8 @@ struct Ctx {
     const int64_t *rowptr = nullptr;
     const int32_t *col = nullptr;
     const double *val = nullptr;
+    DevBuf csr_buf;         // room for a call's copy (mixed word, real parts, columns, row starts); may be empty
+    bool csr_copy = false;  // this call's orders read the copy
     // Holstein (owned device copies)
     bool holstein = false;
     int hol_L = 0, hol_nph = 0;
@@ -278,6 +286,12 @@ int32_t *chain_multi_timeout(const Ctx &c);
 hipError_t launch_chain_small(const Ctx &c, hipStream_t s, double2 *psi, double2 *out, int64_t K, double *norm_out,
                               double *energy_out, double2 *ckpt, double *check, bool *checked);
 hipError_t launch_fill_zero(hipStream_t s, double *p, int64_t count);
+// room for the copy of a real CSR matrix that a call of many orders reads
+// instead of the caller's arrays, whether a call of `orders` orders makes it,
+// and making it
+size_t csr_copy_bytes(int64_t n, int64_t nnz);
+bool csr_copy_pays(const Ctx &c, int64_t orders);
+hipError_t launch_csr_copy(const Ctx &c, hipStream_t s);
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,
                             int64_t nnz, int64_t *flag);
 

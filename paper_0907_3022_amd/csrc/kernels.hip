@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include <cstdint>
+#include <cstdlib>
 
 #include "internal.h"
 #include "device_ops.h"
@@ -81,6 +82,7 @@ __global__ __launch_bounds__(kBlock) void k_head_honey(OpHoney op, const double2
     head_body(i, i >= 0, vi, h2, v1, acc, g0, g1, ckpt, partials);
 }
 
+template <bool COPY>
 __global__ __launch_bounds__(kBlock) void k_head_csr(OpCsr op, const double2 *__restrict__ v0,
                                                      double2 *__restrict__ v1,
                                                      double2 *__restrict__ acc, double2 g0,
@@ -90,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void k_head_csr(OpCsr op, const double2 *__
     double2 vi = make_double2(0.0, 0.0), h2 = vi;
     if (i >= 0) {
         vi = v0[i];
-        h2 = CsrRow::apply2(op, i, v0, vi);
+        h2 = CsrRow::apply2_of<COPY>(op, i, v0, vi);
     }
     head_body(i, i >= 0, vi, h2, v1, acc, g0, g1, ckpt, partials);
 }
@@ -345,6 +347,7 @@ __global__ __launch_bounds__(kBlock) void k_iter_hol(OpHol op, int spt, int rema
 
 // The accumulator as in the Holstein walk: up to three orders' weights at
 // once (nacc terms), none on the other orders.
+template <bool COPY>
 __global__ __launch_bounds__(kBlock) void k_iter_csr(OpCsr op, const double2 *__restrict__ vk,
                                                      double2 *vprev, double2 *__restrict__ acc, int nacc,
                                                      double2 ga, double2 gb, double2 gc)
@@ -352,7 +355,7 @@ __global__ __launch_bounds__(kBlock) void k_iter_csr(OpCsr op, const double2 *__
     const int64_t i = CsrRow::row(op);
     if (i < 0) return;
     const double2 vi = vk[i];
-    const double2 h2 = CsrRow::apply2(op, i, vk, vi);
+    const double2 h2 = CsrRow::apply2_of<COPY>(op, i, vk, vi);
     const double2 p = vprev[i];
     const double2 nv = csub(h2, p);
     vprev[i] = nv;
@@ -498,6 +501,87 @@ hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t 
     hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, s, flag);
     const int64_t nb = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_csr_check, dim3((unsigned)nb), dim3(kBlock), 0, s, rowptr, col, n, nnz, flag);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// A call's copy of a CSR matrix: real parts and columns, the entries of 64
+// rows ordered so that a wavefront's loads are contiguous (copy_slot; no
+// padding), 32-bit row starts, and a word that tells whether any imaginary
+// part is not zero (the orders then read the caller's arrays).  The caller's
+// arrays are only borrowed and may hold other values at the next call, so the
+// copy is made anew in every call.
+//
+// What bounds the orders of a CSR run is the matrix, 20 B an entry of complex
+// values at 32 B strides or more between lanes, against 12 B an entry here,
+// and the gathered vector elements, most of which come from the last-level
+// cache.  The sums keep their order and their bits.  Measured on MI355X, an
+// order of the Holstein ring's 1.85M rows of four entries: 57 -> 43 us (111 B
+// a row and the gathers); the copy takes 1.5 orders.  Real parts alone, in the
+// caller's order, gave 46 us; non-temporal loads of the copy 45 us; one
+// contiguous range of rows per XCD 43 us there but 30% more at 16M rows.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_csr_copy(OpCsr op, int64_t nnz, double *__restrict__ re,
+                                                     int32_t *__restrict__ col32, int32_t *__restrict__ rowptr32,
+                                                     int32_t *mixed)
+{
+    const int64_t i = CsrRow::row(op);
+    if (i < 0) return;
+    const int64_t p0 = op.rowptr[i], p1 = op.rowptr[i + 1];
+    const int32_t len = (int32_t)(p1 - p0);
+    uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)p0);
+    bool im = false;
+    for (int32_t j = 0;; ++j) {
+        const uint64_t mask = __ballot(len > j);
+        if (mask == 0) break;
+        if (len > j) {
+            const double2 h = op.val[p0 + j];
+            const uint32_t at = p + CsrRow::copy_slot(mask);
+            re[at] = h.x;
+            col32[at] = op.col[p0 + j];
+            im |= h.y != 0.0;
+        }
+        p += (uint32_t)__popcll(mask);
+    }
+    rowptr32[i] = (int32_t)p0;
+    if (i == op.n - 1) rowptr32[op.n] = (int32_t)nnz;
+    if (im) *mixed = 1;
+}
+
+__global__ void k_clear_word(int32_t *w) { *w = 0; }
+
+// From eight orders and 2^20 entries on: 64 / 8 / 4 orders of a call take the
+// copy at 1.75M entries 1.28 / 1.09 / 0.96 times as fast as without it, at
+// 7.4M 1.31 / 1.13 / 0.98, at 64M 1.31 / 1.12 / 0.97; at 0.41M entries, which
+// the L2 caches hold, 0.97 / 0.87 / 0.81.
+constexpr int64_t kCsrCopyOrders = 8, kCsrCopyEntries = 1 << 20;
+
+size_t csr_copy_bytes(int64_t n, int64_t nnz)
+{
+    if (nnz < 1 || nnz >= INT32_MAX || (nnz < kCsrCopyEntries && !std::getenv("CHEBTD_CSR_COPY"))) return 0;
+    return 16 + (size_t)nnz * 12 + (size_t)(n + 1) * 4;
+}
+
+bool csr_copy_pays(const Ctx &c, int64_t orders)
+{
+    const size_t need = csr_copy_bytes(c.n, c.nnz);
+    if (c.kind != HKind::Csr || need == 0 || c.csr_buf.bytes < need) return false;
+    if (const char *env = std::getenv("CHEBTD_CSR_COPY")) return std::atoi(env) != 0;
+    return orders >= kCsrCopyOrders && c.nnz >= kCsrCopyEntries;
+}
+
+hipError_t launch_csr_copy(const Ctx &c, hipStream_t s)
+{
+    Ctx v;  // where the copy lies
+    v.csr_copy = true;
+    v.csr_buf = c.csr_buf;
+    v.nnz = c.nnz;
+    const OpCsr op = make_csr(v);
+    hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, s, const_cast<int32_t *>(op.mixed));
+    OpCsr from = make_csr(c);
+    hipLaunchKernelGGL(k_csr_copy, dim3((unsigned)((c.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, from, c.nnz,
+                       const_cast<double *>(op.re), const_cast<int32_t *>(op.col32),
+                       const_cast<int32_t *>(op.rowptr32), const_cast<int32_t *>(op.mixed));
     return hipGetLastError();
 }
 
@@ -765,8 +849,8 @@ hipError_t launch_head(const Ctx &c, hipStream_t s, const double2 *v0, double2 *
                                v1, acc, g0, g1, ckpt, partials);
         break;
     case HKind::Csr:
-        hipLaunchKernelGGL(k_head_csr, grid, block, 0, s, make_csr(c), v0, v1, acc, g0, g1, ckpt,
-                           partials);
+        hipLaunchKernelGGL(c.csr_copy ? k_head_csr<true> : k_head_csr<false>, grid, block, 0, s, make_csr(c), v0, v1,
+                           acc, g0, g1, ckpt, partials);
         break;
     default:
         return hipErrorInvalidValue;
@@ -804,8 +888,8 @@ hipError_t launch_iter_lazy(const Ctx &c, hipStream_t s, const double2 *vk, doub
 {
     if ((c.kind != HKind::Holstein && c.kind != HKind::Csr) || nacc < 0 || nacc > 3) return hipErrorInvalidValue;
     if (c.kind == HKind::Csr) {
-        hipLaunchKernelGGL(k_iter_csr, dim3((unsigned)grid_blocks(c)), dim3(kBlock), 0, s, make_csr(c), vk, vprev, acc,
-                           nacc, ga, gb, gc);
+        hipLaunchKernelGGL(c.csr_copy ? k_iter_csr<true> : k_iter_csr<false>, dim3((unsigned)grid_blocks(c)),
+                           dim3(kBlock), 0, s, make_csr(c), vk, vprev, acc, nacc, ga, gb, gc);
         return hipGetLastError();
     }
     return launch_hol_walk(c, s, false, vk, vprev, acc, nacc, ga, gb, gc, nullptr, nullptr);

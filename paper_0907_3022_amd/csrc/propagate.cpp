@@ -310,7 +310,7 @@ int get_pair_graph(Ctx *c, double2 *psi, double *norm_out, double *energy_out, u
                    hipGraphExec_t *out)
 {
     const void *key[4] = {psi, norm_out, energy_out,
-                          reinterpret_cast<const void *>((uintptr_t)(flags & CHEBTD_SINGLE_ORDER) + 1)};
+                          reinterpret_cast<const void *>((uintptr_t)(flags & CHEBTD_SINGLE_ORDER) + (c->csr_copy ? 2 : 1))};
     if (c->graph_exec[0] && key[0] == c->graph_key[0] && key[1] == c->graph_key[1] &&
         key[2] == c->graph_key[2] && key[3] == c->graph_key[3]) {
         *out = c->graph_exec[0];
@@ -379,6 +379,17 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     double2 *P = reinterpret_cast<double2 *>(psi_dev);
     double2 *B = static_cast<double2 *>(c->vB.p);
     hipError_t e = hipSuccess;
+
+    // a real CSR matrix: this call's orders read a copy of it
+    struct CopyUse {
+        Ctx *c;
+        ~CopyUse() { c->csr_copy = false; }
+    } copy_use{c};
+    if (csr_copy_pays(*c, K * (int64_t)std::max(c->M, 1))) {
+        e = launch_csr_copy(*c, s);
+        if (e != hipSuccess) return hip_fail(c, e, "matrix copy");
+        c->csr_copy = true;
+    }
 
     // the one-workgroup chain kernel keeps psi_s but not the step-end pairs
     const bool small = c->kind == HKind::Chain && chain_small_fits(c->n) &&
