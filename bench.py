@@ -6,17 +6,18 @@ ribbon (1,048,576 sites, Anderson disorder W = 0.5, dt = 1, Chebyshev order
 M = 20 from the 1e-15 Bessel cutoff).  One step is the whole hot path: the
 step head (v_1 = H~ psi, acc = gamma_0 psi + gamma_1 v_1, norm and energy
 reductions) and the recursion v_{k+1} = 2 H~ v_k - v_{k-1},
-acc += gamma_{k+1} v_{k+1} up to order M, several orders per pass over memory
-(the split the library plans, reported as config.orders_per_pass).  The plan (bounds,
+acc += gamma_{k+1} v_{k+1} up to order M, all of them in one pass over memory
+(k_pipe; config.orders_per_pass).  The plan (bounds,
 Bessel weights, passes) is computed once per dt, outside the timed region, as
 the method prescribes.
 
 value = Hamiltonian applications (H~ v products) per second.
-roofline: the dominant recursion kernel's algorithmic bytes (104 B per site
-and pass, whatever the orders per pass: v_{k-1}, v_k, on-site term and acc
-read, the last two vectors and acc written; 88 B per site for a
-single-order pass) over its mean launch time measured with HIP events on the
-library's stream.
+roofline: the dominant recursion kernel's algorithmic bytes (pass_bytes: 40 B
+per site for a step in one pass: psi and the on-site term read, psi written;
+88 B per site for a single-order pass) over its mean launch time measured with
+HIP events on the library's stream, and its useful FP64 operations (20 per
+site and order) over the same time: with all orders of a step in one pass the
+kernel is bound by FP64 issue, not by HBM.
 cpu_baseline: the serial CPU oracle on a few steps of the same workload.
 """
 from __future__ import annotations
@@ -39,7 +40,8 @@ import workloads as W  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0
 STENCIL_BYTES = 88       # per site and order: v_k, v_{k-1}, v_{k+1}, acc r/w, on-site term
-PAIR_BYTES = 104         # per site and multi-order pass: v_{k-1}, v_k, on-site, acc r/w, last two vectors
+FP64_PEAK_TFLOPS = 78.6  # vector FP64
+ORDER_FLOPS = 20         # per site and order: 2 H~ v - v_{k-1} of three neighbours and the weighted sum
 CSR_VEC_BYTES = 80       # vector traffic per row and order for CSR
 CSR_NNZ_BYTES = 20       # complex128 value + int32 column
 CSR_ROW_BYTES = 8        # rowptr
@@ -48,6 +50,17 @@ HOL_CSR_BYTES = CSR_VEC_BYTES + 4 * CSR_NNZ_BYTES + CSR_ROW_BYTES  # the same ro
 
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
+
+
+def pass_bytes(orders, M):
+    """Mean bytes per site of a step's passes of `orders` orders: one pass
+    reads psi and the on-site term and writes psi; otherwise the first reads
+    those and writes two vectors and acc, the last reads two vectors, acc and
+    the on-site term and writes acc, and those between do both (104 B)."""
+    if orders < 2:
+        return STENCIL_BYTES
+    p = -(-M // orders)
+    return 40 if p == 1 else (72 + 72 + 104 * (p - 2)) / p
 
 
 def source_hash():
@@ -124,7 +137,6 @@ def bench_main(torch, P, steps, warmup, mode_flags):
     psi2 = psi.clone()
     t_single = timed(torch, lambda: ctx.propagate(psi2, steps, nrm, en, flags | P.SINGLE_ORDER))
     return dict(ctx=ctx, n=n, M=M, seconds=t, ms_iter=ms_iter, kernel=kname, orders=orders,
-                passes=ctx.plan_passes(),
                 ms_single=ms_single, kernel_single=kname_single, seconds_single=t_single,
                 norm_drift=drift, psi=psi, eps=eps_d)
 
@@ -360,10 +372,11 @@ def bench_sweep(torch, P, sizes):
         ms, kname, orders = ctx.time_recursion_kernel(50)
         ms1, kname1, _ = ctx.time_recursion_kernel(50, P.SINGLE_ORDER)
         n = width * length
-        per = PAIR_BYTES if orders >= 2 else STENCIL_BYTES
-        res.append(dict(sites=n, shape=f"{width}x{length}", kernel=kname, kernel_ms=ms, passes=ctx.plan_passes(),
+        per = pass_bytes(orders, M)
+        res.append(dict(sites=n, shape=f"{width}x{length}", kernel=kname, kernel_ms=ms,
                         orders_per_launch=orders, GBs=per * n / (ms * 1e-3) / 1e9,
                         ns_per_site_order=ms * 1e6 / n / orders,
+                        fp64_tflops=ORDER_FLOPS * orders * n / (ms * 1e-3) / 1e12,
                         single_order_kernel_ms=ms1, single_order_GBs=STENCIL_BYTES * n / (ms1 * 1e-3) / 1e9))
         ctx.close()
         del eps_d, psi
@@ -409,26 +422,16 @@ def bench_batched(torch, P, K, seq_steps=10):
     batched_rate = site_orders * K / t
     seq_rate = site_orders * seq_steps / seq_t
     mode = ["levels", "persistent", "pairs", "deep"][best[0]]
-    # algorithmic bytes of one step: 88 per site and order, or 104 per site
-    # and multi-order pass plus 88 for an odd tail (the deep schedule: the
-    # fewest passes of `depth` or `depth` + 1 orders that cover M, else
-    # M // depth passes taking up to one extra order each, then pairs)
-    if mode in ("pairs", "deep"):
-        depth = int(os.environ.get("CHEBTD_BATCH_DEPTH", "5")) if mode == "deep" else 2
-
-        def passes(M):
-            nd, ext = 0, 0
-            if mode == "deep":
-                E = depth + 1 if depth < 6 else 0
-                if E and depth * (-(-M // E)) <= M:
-                    nd = -(-M // E)
-                    ext = M - depth * nd
-                else:
-                    nd = M // depth
-                    ext = min(M - depth * nd, nd) if E else 0
-            rest = M - nd * depth - ext
-            return nd + rest // 2, rest % 2
-        step_bytes = sum(s["width"] * s["length"] * (PAIR_BYTES * passes(int(M))[0] + STENCIL_BYTES * passes(int(M))[1])
+    # algorithmic bytes of one step: 88 per site and order; 104 per site and
+    # pass of two orders plus 88 for an odd last one; the deep schedule's
+    # pipelined passes take up to 24 orders each (pass_bytes)
+    if mode == "deep":
+        def site_bytes(M):
+            p = -(-M // 24)
+            return p * pass_bytes(-(-M // p), M)
+        step_bytes = sum(s["width"] * s["length"] * site_bytes(int(M)) for s, M in zip(systems, Ms))
+    elif mode == "pairs":
+        step_bytes = sum(s["width"] * s["length"] * (104 * (int(M) // 2) + STENCIL_BYTES * (int(M) % 2))
                          for s, M in zip(systems, Ms))
     else:
         step_bytes = STENCIL_BYTES * site_orders
@@ -437,7 +440,8 @@ def bench_batched(torch, P, K, seq_steps=10):
                 M_min=int(Ms.min()), M_max=int(Ms.max()), steps=K, seconds=t,
                 schedule=dict(mode=mode, tile=best[1], block=best[2], wg_per_cu=best[3]),
                 autotune_seconds=tune_s, site_orders_per_s=batched_rate,
-                GBs=step_bytes * K / t / 1e9, GBs_at_88B_per_site_order=STENCIL_BYTES * batched_rate / 1e9,
+                GBs=step_bytes * K / t / 1e9, fp64_tflops=ORDER_FLOPS * batched_rate / 1e12,
+                GBs_at_88B_per_site_order=STENCIL_BYTES * batched_rate / 1e9,
                 sequential_site_orders_per_s=seq_rate, sequential_steps=seq_steps,
                 speedup_vs_sequential=batched_rate / seq_rate)
 
@@ -546,13 +550,13 @@ def bench_table2(torch, P):
     return dict(workload=W.TABLE2.name, W=p["W"], seed=p["seed"], runs=runs)
 
 
-def bench_shard(torch, P, gpus=(1, 2, 4, 8), shapes=((128, 8192), (1024, 65536)), D=5):
+def bench_shard(torch, P, gpus=(1, 2, 4, 8), shapes=((128, 8192), (1024, 65536)), D=20):
     """One GPU's share of a ribbon cut into N slabs along its length (the
     sharding the design describes; the library runs on one GPU): the dominant
     pass timed on a slab of L/N columns plus D halo columns on each side that
-    the pass recomputes (D = its orders, 5 for these M = 20 ribbons), and the
-    halo a pass would exchange per side: D columns of v_{k-1} and v_k,
-    2 D W 16 bytes.  No exchange is run or timed here."""
+    the pass recomputes (D = its orders, all 20 of these ribbons' steps), and
+    the halo a step would exchange per side: D columns of psi, D W 16 bytes.
+    No exchange is run or timed here."""
     out = []
     for (w, l) in shapes:
         for n in gpus:
@@ -564,14 +568,14 @@ def bench_shard(torch, P, gpus=(1, 2, 4, 8), shapes=((128, 8192), (1024, 65536))
             lo, hi = ctx.gershgorin()
             ctx.set_bounds(lo, hi)
             M = ctx.plan(1.0)
-            passes = ctx.plan_passes()
-            assert max(passes) == D, passes
             ms, name, orders = ctx.time_recursion_kernel(100 if w * cols <= (1 << 22) else 20)
+            passes = -(-M // orders)
+            assert M <= D and passes == 1, (M, orders)
             ctx.close()
             del eps_d
             out.append(dict(ribbon=f"{w}x{l}", gpus=n, slab=f"{w}x{cols}", M=M, passes=passes, kernel=name,
-                            us_per_pass=ms * 1e3, step_us_compute=ms * 1e3 * len(passes),
-                            halo_bytes_per_pass_per_side=2 * halo * w * 16))
+                            us_per_pass=ms * 1e3, step_us_compute=ms * 1e3 * passes,
+                            halo_bytes_per_step_per_side=halo * w * 16))
         torch.cuda.empty_cache()
     return out
 
@@ -730,7 +734,8 @@ def main():
     r = bench_main(torch, P, args.steps, args.warmup, mode_flags)
     hv = args.steps * r["M"]
     value = hv / r["seconds"] if r["seconds"] > 0 else 0.0
-    unit_bytes = PAIR_BYTES if r["orders"] >= 2 else STENCIL_BYTES
+    unit_bytes = pass_bytes(r["orders"], r["M"])
+    tflops = ORDER_FLOPS * r["orders"] * r["n"] / (r["ms_iter"] * 1e-3) / 1e12
     achieved = unit_bytes * r["n"] / (r["ms_iter"] * 1e-3) / 1e9
     traffic = traffic_record(r["kernel"])
     line = {
@@ -748,8 +753,11 @@ def main():
         "data": "synthetic",
         "config": {"workload": "zigzag_ribbon_128x8192", "sites": r["n"], "disorder_W": 0.5,
                    "dt": 1.0, "chebyshev_order": r["M"], "time_steps": args.steps,
-                   "launch_mode": mode_name, "orders_per_pass": r["passes"], "complex128": True},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                   "launch_mode": mode_name, "orders_per_pass": r["orders"], "complex128": True},
+        "roofline": {"bound": "hbm", "limiter": "fp64 issue",
+                     "fp64_tflops": tflops, "fp64_peak_tflops": FP64_PEAK_TFLOPS,
+                     "fp64_frac": tflops / FP64_PEAK_TFLOPS,
+                     "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": r["kernel"], "kernel_ms_per_launch": r["ms_iter"],
                      "orders_per_launch": r["orders"],

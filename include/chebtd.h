@@ -421,10 +421,12 @@ int chebtd_adjoint_run(chebtd_ctx *ctx, int64_t run_id, double *gbar_dev, double
  * times on the context's stream between two hipEvents, on scratch vectors
  * (allocated and freed here), and return the mean time per launch in
  * milliseconds, the kernel's name and the recursion orders one launch
- * advances.  On the multi-order path that is the pass the step runs most
- * often after its head (chebtd_plan_passes; 2 for the two-orders kernel, 3..6
- * for the deep kernel), else 1; CHEBTD_SINGLE_ORDER in `flags` times the
- * one-order kernel.  The Holstein and CSR kernels are timed in the pattern a
+ * advances.  On chains and ribbons whose steps run in pipelined or tiled
+ * passes whole steps are run and the mean time of their passes is returned,
+ * with the name and orders of the pass they run most often; past the sizes of
+ * those, the multi-order pass of chebtd_plan_passes that a step runs most
+ * often after its head.  1 elsewhere; CHEBTD_SINGLE_ORDER in `flags` times
+ * the one-order kernel.  The Holstein and CSR kernels are timed in the pattern a
  * step runs them: two launches without the accumulator for every one that
  * updates it with three orders.  Needs a plan.  Synchronises.
  * name_out and orders_out may be NULL. */

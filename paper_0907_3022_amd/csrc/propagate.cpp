@@ -5,6 +5,7 @@
 // next state.  Buffers rotate so that no copy is made inside the K steps.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -148,6 +149,34 @@ int step_blocks(const Ctx &c, bool ends, bool last)
     }
     const std::vector<PipeShape> &p = ends ? c.pipe_ends : c.pipe;
     return (int)pipe_blocks(c, last ? p.back() : p.front());
+}
+
+// Passes of such a step, the kernel of most of them and the orders of one.
+const char *pipe_names(const Ctx &c, int *npass, int *orders)
+{
+    static const char *const tiles[] = {"k_chain_tile<2>",     "k_chain_tile<4>",     "k_chain_tile<8>",
+                                        "k_ribbon_tile<0, 2>", "k_ribbon_tile<0, 4>", "k_ribbon_tile<0, 6>",
+                                        "k_ribbon_tile<1, 2>", "k_ribbon_tile<1, 4>", "k_ribbon_tile<1, 6>"};
+    static const char *const pipes[] = {"k_pipe<0, 2, 4>", "k_pipe<0, 3, 4>", "k_pipe<0, 4, 4>", "k_pipe<0, 5, 4>",
+                                        "k_pipe<0, 3, 8>", "k_pipe<1, 2, 4>", "k_pipe<1, 3, 4>", "k_pipe<1, 4, 4>",
+                                        "k_pipe<1, 5, 4>", "k_pipe<1, 3, 8>"};
+    const int arm = c.kind == HKind::Honeycomb && c.edge == CHEBTD_ARMCHAIR;
+    if (c.tile.R) {
+        *npass = (int)c.tile.depths.size();
+        *orders = *std::max_element(c.tile.depths.begin(), c.tile.depths.end());
+        if (c.kind == HKind::Chain) return tiles[c.tile.R == 2 ? 0 : c.tile.R == 4 ? 1 : 2];
+        return tiles[3 + 3 * arm + c.tile.R / 2 - 1];
+    }
+    auto count = [&](const PipeShape &a) {
+        return std::count_if(c.pipe.begin(), c.pipe.end(),
+                             [&](const PipeShape &b) { return a.DW == b.DW && a.NW == b.NW; });
+    };
+    const PipeShape &sh = *std::max_element(c.pipe.begin(), c.pipe.end(), [&](const PipeShape &a, const PipeShape &b) {
+        return count(a) < count(b);
+    });
+    *npass = (int)c.pipe.size();
+    *orders = std::min(sh.depth(), c.M);
+    return pipes[5 * arm + (sh.NW == 8 ? 4 : sh.DW - 2)];
 }
 
 // One time step cur -> nxt in pipelined passes; partials: the head's norm and
@@ -607,7 +636,8 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     Ctx *c = static_cast<Ctx *>(ctx);
     if (!c->has_plan) return fail(c, CHEBTD_E_STATE, "chebtd_time_recursion_kernel: no plan");
     if (launches < 1 || !ms_per_launch) return fail(c, CHEBTD_E_ARG, "need launches >= 1 and an output");
-    const bool pairs = c->use_pairs && !(flags & CHEBTD_SINGLE_ORDER);
+    const bool pipe = use_pipe(*c, flags, false);
+    const bool pairs = !pipe && c->use_pairs && !(flags & CHEBTD_SINGLE_ORDER);
     // the multi-order kernel the step spends most of its passes in
     const int dp = pairs ? dominant_pass(*c) : 2;
     static const char *names[] = {"k_iter_chain", "k_iter_honey<0>", "k_iter_honey<1>", "k_iter_csr",
@@ -629,8 +659,13 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
                      : c->kind == HKind::Csr      ? names[3]
                      : c->kind == HKind::Holstein ? names[c->hol_brows > 0 ? 6 : 7]
                      : (c->edge == CHEBTD_ZIGZAG ? names[1] : names[2]);
+    int npass = 1, orders = pairs ? dp : 1;
+    if (pipe) {
+        nm = pipe_names(*c, &npass, &orders);
+        launches = (launches + npass - 1) / npass;  // whole steps
+    }
     if (name_out) *name_out = nm;
-    if (orders_out) *orders_out = pairs ? dp : 1;
+    if (orders_out) *orders_out = orders;
     // scratch: four vectors and an accumulator, zeroed
     DevBuf scratch;
     const size_t vb = (size_t)c->n * sizeof(double2);
@@ -644,6 +679,9 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     for (int j = 0; j <= dp; ++j) gd[j] = weight(c, j < 1 ? 1 : j);
     gd[0] = make_double2(0.0, 0.0);
     auto one = [&](int i) -> hipError_t {
+        if (pipe)
+            return enqueue_step_pipe(c, s, (i & 1) ? V1 : V0, (i & 1) ? V0 : V1, nullptr, nullptr, c->pipe_sums,
+                                     nullptr);
         if (pairs && dp > 2)
             return (i & 1) ? launch_deep(*c, s, dp, c->deep_rows[dp], false, V2, V3, V0, V1, acc, gd, nullptr,
                                          nullptr, nullptr)
@@ -668,7 +706,7 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, c->ev_a, c->ev_b);
     release(scratch);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_time_recursion_kernel");
-    *ms_per_launch = (double)ms / launches;
+    *ms_per_launch = (double)ms / launches / npass;
     return CHEBTD_OK;
 }
 
