@@ -226,7 +226,7 @@ struct CsrRow {
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
     }
     // the same as apply2 from the copy of a real matrix: the sum in the same order
-    __device__ static __forceinline__ double2 apply2_real(const OpCsr &op, int64_t i, const double2 *v, double2 vi)
+    __device__ static __forceinline__ double2 apply2_real(const OpCsrCopy &op, int64_t i, const double2 *v, double2 vi)
     {
         const int32_t p0 = op.rowptr32[i], len = op.rowptr32[i + 1] - p0;
         const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane(p0);
@@ -256,11 +256,13 @@ struct CsrRow {
         }
         return make_double2(op.s2 * fma(-op.b, vi.x, sx), op.s2 * fma(-op.b, vi.y, sy));
     }
-    template <bool COPY>
     __device__ static __forceinline__ double2 apply2_of(const OpCsr &op, int64_t i, const double2 *v, double2 vi)
     {
-        if (COPY && *op.mixed == 0) return apply2_real(op, i, v, vi);
         return apply2(op, i, v, vi);
+    }
+    __device__ static __forceinline__ double2 apply2_of(const OpCsrCopy &op, int64_t i, const double2 *v, double2 vi)
+    {
+        return *op.mixed == 0 ? apply2_real(op, i, v, vi) : apply2(op, i, v, vi);
     }
 };
 
@@ -339,19 +341,21 @@ inline OpCsr make_csr(const Ctx &c)
     op.rowptr = c.rowptr;
     op.col = c.col;
     op.val = reinterpret_cast<const double2 *>(c.val);
-    op.rowptr32 = op.col32 = nullptr;
-    op.re = nullptr;
-    op.mixed = nullptr;
-    if (c.csr_copy) {
-        char *p = static_cast<char *>(c.csr_buf.p);
-        op.mixed = reinterpret_cast<const int32_t *>(p);
-        op.re = reinterpret_cast<const double *>(p + 16);
-        op.col32 = reinterpret_cast<const int32_t *>(p + 16 + (size_t)c.nnz * 8);
-        op.rowptr32 = op.col32 + c.nnz;
-    }
     op.b = c.b;
     op.s2 = 2.0 / c.a;
     op.n = c.n;
+    return op;
+}
+
+inline OpCsrCopy make_csr_copy(const Ctx &c)
+{
+    OpCsrCopy op;
+    static_cast<OpCsr &>(op) = make_csr(c);
+    char *p = static_cast<char *>(c.csr_buf.p);
+    op.mixed = reinterpret_cast<const int32_t *>(p);
+    op.re = reinterpret_cast<const double *>(p + 16);
+    op.col32 = reinterpret_cast<const int32_t *>(p + 16 + (size_t)c.nnz * 8);
+    op.rowptr32 = op.col32 + c.nnz;
     return op;
 }
 

@@ -72,15 +72,18 @@ struct OpCsr {
     const int64_t *rowptr;
     const int32_t *col;
     const double2 *val;
-    // a call's copy of a real matrix (k_csr_copy): 32-bit row starts, columns
-    // and real parts in the order the orders read them, and a word that is not
-    // 0 if an imaginary part is
-    const int32_t *rowptr32, *col32;
-    const double *re;
-    const int32_t *mixed;
     double b;
     double s2;  // 2/a
     int64_t n;
+};
+
+// With a call's copy of a real matrix (k_csr_copy): 32-bit row starts, columns
+// and real parts in the order the orders read them, and a word that is not 0
+// if an imaginary part is.
+struct OpCsrCopy : OpCsr {
+    const int32_t *rowptr32, *col32;
+    const double *re;
+    const int32_t *mixed;
 };
 
 // ---------------------------------------------------------------------------
@@ -225,7 +228,10 @@ int holstein_build(int L, int nph, double t, double w0, const double *g, const d
 // Kernel launchers (kernels.hip).  All enqueue on `s` and return hipError_t.
 // ---------------------------------------------------------------------------
 constexpr int kBlock = 256;
-constexpr size_t kStepSumBytes = size_t(1) << 20;
+// Step sums in flight.  A quarter MiB: with a whole one the runtime, which takes
+// small allocations from 2 MiB chunks, needs a chunk more per context (60 us
+// for creating and destroying it); rings of 8 or 32 steps run alike.
+constexpr size_t kStepSumBytes = size_t(1) << 18;
 // LDS the Holstein walk may give its binomial table (beyond it, the walk
 // reads the per-state partner tables instead)
 constexpr int kHolBinomBytes = 16384;

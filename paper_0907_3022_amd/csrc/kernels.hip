@@ -82,8 +82,8 @@ __global__ __launch_bounds__(kBlock) void k_head_honey(OpHoney op, const double2
     head_body(i, i >= 0, vi, h2, v1, acc, g0, g1, ckpt, partials);
 }
 
-template <bool COPY>
-__global__ __launch_bounds__(kBlock) void k_head_csr(OpCsr op, const double2 *__restrict__ v0,
+template <class Op>
+__global__ __launch_bounds__(kBlock) void k_head_csr(Op op, const double2 *__restrict__ v0,
                                                      double2 *__restrict__ v1,
                                                      double2 *__restrict__ acc, double2 g0,
                                                      double2 g1, double2 *ckpt, double *partials)
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kBlock) void k_head_csr(OpCsr op, const double2 *__
     double2 vi = make_double2(0.0, 0.0), h2 = vi;
     if (i >= 0) {
         vi = v0[i];
-        h2 = CsrRow::apply2_of<COPY>(op, i, v0, vi);
+        h2 = CsrRow::apply2_of(op, i, v0, vi);
     }
     head_body(i, i >= 0, vi, h2, v1, acc, g0, g1, ckpt, partials);
 }
@@ -347,15 +347,15 @@ __global__ __launch_bounds__(kBlock) void k_iter_hol(OpHol op, int spt, int rema
 
 // The accumulator as in the Holstein walk: up to three orders' weights at
 // once (nacc terms), none on the other orders.
-template <bool COPY>
-__global__ __launch_bounds__(kBlock) void k_iter_csr(OpCsr op, const double2 *__restrict__ vk,
+template <class Op>
+__global__ __launch_bounds__(kBlock) void k_iter_csr(Op op, const double2 *__restrict__ vk,
                                                      double2 *vprev, double2 *__restrict__ acc, int nacc,
                                                      double2 ga, double2 gb, double2 gc)
 {
     const int64_t i = CsrRow::row(op);
     if (i < 0) return;
     const double2 vi = vk[i];
-    const double2 h2 = CsrRow::apply2_of<COPY>(op, i, vk, vi);
+    const double2 h2 = CsrRow::apply2_of(op, i, vk, vi);
     const double2 p = vprev[i];
     const double2 nv = csub(h2, p);
     vprev[i] = nv;
@@ -572,14 +572,9 @@ bool csr_copy_pays(const Ctx &c, int64_t orders)
 
 hipError_t launch_csr_copy(const Ctx &c, hipStream_t s)
 {
-    Ctx v;  // where the copy lies
-    v.csr_copy = true;
-    v.csr_buf = c.csr_buf;
-    v.nnz = c.nnz;
-    const OpCsr op = make_csr(v);
+    const OpCsrCopy op = make_csr_copy(c);
     hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, s, const_cast<int32_t *>(op.mixed));
-    OpCsr from = make_csr(c);
-    hipLaunchKernelGGL(k_csr_copy, dim3((unsigned)((c.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, from, c.nnz,
+    hipLaunchKernelGGL(k_csr_copy, dim3((unsigned)((c.n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, make_csr(c), c.nnz,
                        const_cast<double *>(op.re), const_cast<int32_t *>(op.col32),
                        const_cast<int32_t *>(op.rowptr32), const_cast<int32_t *>(op.mixed));
     return hipGetLastError();
@@ -849,8 +844,12 @@ hipError_t launch_head(const Ctx &c, hipStream_t s, const double2 *v0, double2 *
                                v1, acc, g0, g1, ckpt, partials);
         break;
     case HKind::Csr:
-        hipLaunchKernelGGL(c.csr_copy ? k_head_csr<true> : k_head_csr<false>, grid, block, 0, s, make_csr(c), v0, v1,
-                           acc, g0, g1, ckpt, partials);
+        if (c.csr_copy)
+            hipLaunchKernelGGL(k_head_csr<OpCsrCopy>, grid, block, 0, s, make_csr_copy(c), v0, v1, acc, g0, g1, ckpt,
+                               partials);
+        else
+            hipLaunchKernelGGL(k_head_csr<OpCsr>, grid, block, 0, s, make_csr(c), v0, v1, acc, g0, g1, ckpt,
+                               partials);
         break;
     default:
         return hipErrorInvalidValue;
@@ -888,8 +887,12 @@ hipError_t launch_iter_lazy(const Ctx &c, hipStream_t s, const double2 *vk, doub
 {
     if ((c.kind != HKind::Holstein && c.kind != HKind::Csr) || nacc < 0 || nacc > 3) return hipErrorInvalidValue;
     if (c.kind == HKind::Csr) {
-        hipLaunchKernelGGL(c.csr_copy ? k_iter_csr<true> : k_iter_csr<false>, dim3((unsigned)grid_blocks(c)),
-                           dim3(kBlock), 0, s, make_csr(c), vk, vprev, acc, nacc, ga, gb, gc);
+        const dim3 grid((unsigned)grid_blocks(c)), block(kBlock);
+        if (c.csr_copy)
+            hipLaunchKernelGGL(k_iter_csr<OpCsrCopy>, grid, block, 0, s, make_csr_copy(c), vk, vprev, acc, nacc, ga, gb,
+                               gc);
+        else
+            hipLaunchKernelGGL(k_iter_csr<OpCsr>, grid, block, 0, s, make_csr(c), vk, vprev, acc, nacc, ga, gb, gc);
         return hipGetLastError();
     }
     return launch_hol_walk(c, s, false, vk, vprev, acc, nacc, ga, gb, gc, nullptr, nullptr);
