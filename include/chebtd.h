@@ -57,10 +57,9 @@ extern "C" {
 #define CHEBTD_GRAPH 4u            /* replay each pair of steps from a     */
                                    /* captured hipGraph                     */
 #define CHEBTD_NO_PERSISTENT 8u    /* chains of n <= 4096: passes launched  */
-                                   /* per step instead of the whole run in  */
-                                   /* one launch                            */
+                                   /* per step instead of whole runs        */
 #define CHEBTD_SINGLE_ORDER 16u    /* chains and ribbons: one recursion     */
-                                   /* order per pass instead of two         */
+                                   /* order per pass instead of many        */
 
 typedef struct chebtd_ctx chebtd_ctx;
 
@@ -111,7 +110,10 @@ int chebtd_h_honeycomb(chebtd_ctx *ctx, int64_t width, int64_t length, int edge,
  * (interleaved), all device arrays (borrowed).  The structure is checked on
  * the device (synchronises): CHEBTD_E_ARG if rowptr does not run from 0 to
  * nnz without decreasing or a column lies outside [0, n).  The values must
- * describe a Hermitian matrix; that is not checked. */
+ * describe a Hermitian matrix; that is not checked.  From 2^20 entries on
+ * this takes room on the device (12 B an entry, 4 B a row, if that is at most
+ * an eighth of what is free) in which calls of eight orders or more put a
+ * copy of a real matrix. */
 int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_dev,
                  const int32_t *col_dev, const double *val_dev);
 
@@ -184,9 +186,11 @@ int chebtd_plan_order(chebtd_ctx *ctx, double dt, int M);
 int chebtd_get_plan(const chebtd_ctx *ctx, double *gamma_host, double *a, double *b,
                     double *dt, int *M);
 
-/* The passes of one step on the multi-order path (1D chains longer than
- * the whole-run chain kernels, honeycomb ribbons; M >= 2): the Chebyshev
- * orders each pass advances, in launch order.  The first pass is the step
+/* How M splits into single-wavefront passes (1D chains longer than the
+ * whole-run chain kernels, honeycomb ribbons; M >= 2): the Chebyshev orders
+ * each pass advances, in launch order.  Steps run this split where the
+ * pipelined and tiled passes of 8 and more orders do not (lattices past their
+ * 32-bit offsets, a forced CHEBTD_DEPTH); those are planned beside it.  The first pass is the step
  * head (it also forms v_1 from psi); 2 runs the two-orders kernel, 3..6 the
  * deep kernel (that many orders of the recursion of Sect. 2.2 in one pass
  * over memory), 1 a single-order pass, only ever last.  The split is the
@@ -211,7 +215,7 @@ int chebtd_plan_passes(const chebtd_ctx *ctx, int *passes_out, int capacity, int
  * CHEBTD_KEEP_CHECKPOINTS stores psi_s for the adjoint (CHEBTD_ADJ_REVERSE:
  * also v_{M-1} and v_M of every step); it needs chebtd_reserve_adjoint with
  * K <= its max_steps.
- * A 1D chain of 129 .. 4096 sites runs the whole call in one launch over
+ * A 1D chain of 129 .. 4096 sites runs up to 256 steps per launch over
  * several workgroups that wait on each other (bounded to two seconds per
  * wait): if a wait runs out (workgroups not all resident, e.g. beside other
  * work filling the GPU) psi is left NaN and, unless CHEBTD_NO_CHECK is set,
@@ -314,13 +318,14 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
                                   /* over every system still active (needs  */
                                   /* M >= 2 everywhere), plus one tail      */
                                   /* launch for systems with odd M           */
-#define CHEBTD_SCHED_DEEP 3       /* passes of D (5; 4..6 by environment  */
-                                  /* CHEBTD_BATCH_DEPTH) or D + 1 orders:   */
-                                  /* each system takes the fewest that     */
-                                  /* cover its M, one launch per pass and   */
-                                  /* depth, then two-order and one-order    */
-                                  /* passes for what is left (needs M >= D  */
-                                  /* everywhere)                            */
+#define CHEBTD_SCHED_DEEP 3       /* pipelined passes of 8 to 24 orders,    */
+                                  /* one launch per pass and shape over the */
+                                  /* systems it concerns.  Environment      */
+                                  /* CHEBTD_BATCH_DEPTH=D (4..6): passes of */
+                                  /* D or D + 1 orders, the fewest that     */
+                                  /* cover each M, then two-order and       */
+                                  /* one-order passes.  Needs M >= D (5)    */
+                                  /* everywhere                             */
 
 /* Fix the schedule: mode, rows per tile (multiple of block, >= block),
  * threads per block (64..1024, multiple of 64), and for the persistent
