@@ -605,7 +605,8 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         if (b->M[s] < 2) b->pairs_ok = false;  // the head of a pair level computes two orders
         sd.npass_pairs = b->M[s] >> 1;
     }
-    // deep schedule: passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
+    // deep schedule without the pipelined passes (a forced depth, systems past
+    // their offsets): passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
     // overrides) or D + 1 orders, so every system needs M >= D.  On these
     // HBM-bound passes a pass costs about the same whatever its depth
     // (measured on MI355X over the 256-ribbon workload: 1020, 1024 and 1062
