@@ -541,6 +541,21 @@ ChainMultiCfg chain_multi_config(int64_t n)
     return cfg;
 }
 
+// Whether the workgroups of such a run may keep its weights (wbytes) in LDS.
+// They wait on each other, so all P must be resident, also beside the runs of
+// other streams: as many runs as the device's four hardware queues can start
+// at once have to fit.  With 4096 sites (P = 94) two workgroups fill a CU's LDS
+// from M = 6,700 on and one from 10,100 on, where three runs no longer fit the
+// 256 CUs together and each may hold a part of them until its waits run out.
+// Weights read from memory leave room for all of them; measured on MI355X an
+// order then takes 0.123 us instead of 0.106 (n = 4096, M = 10,500 to 21,000).
+constexpr int kChainRuns = 4;
+bool chain_weights_in_lds(int64_t P, size_t wbytes, int64_t num_cus, size_t lds_per_cu)
+{
+    const size_t per_cu = lds_per_cu / (wbytes + 1024);  // beside a few hundred bytes of its own
+    return num_cus * (int64_t)per_cu >= kChainRuns * P;
+}
+
 namespace {
 constexpr size_t kChainIntBytes = 64;  // sync
 
@@ -649,6 +664,10 @@ hipError_t launch_chain_small(const Ctx &c, hipStream_t s, double2 *psi, double2
         if (const char *env = std::getenv("CHEBTD_CHAIN_SPIN")) limit = std::max<int64_t>(0, std::atoll(env));
         ChainXDev x = chain_x_layout(c, cfg, limit);
         double *const part = x.part, *const knorm = x.knorm;
+        int cu_lds = 0;
+        if (hipDeviceGetAttribute(&cu_lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, c.device) != hipSuccess)
+            cu_lds = max_lds;
+        const size_t wdyn = dyn && chain_weights_in_lds(cfg.P, dyn, c.num_cus, (size_t)cu_lds) ? dyn : 0;
         const int64_t words = chain_x_words(cfg);
         for (int64_t st = 0; st < K; st += kChainRing) {
             const int64_t k = std::min<int64_t>(kChainRing, K - st);
@@ -659,7 +678,7 @@ hipError_t launch_chain_small(const Ctx &c, hipStream_t s, double2 *psi, double2
             hipLaunchKernelGGL(k_chain_multi_clear, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, x.xbuf,
                                words, x.sync, st == 0 ? 1 : 0);
             hipError_t e = launch_chain_multi(c, s, op, cfg, x, st == 0 ? psi : out, out, k,
-                                              ckpt ? ckpt + (size_t)st * c.n : nullptr, dyn);
+                                              ckpt ? ckpt + (size_t)st * c.n : nullptr, wdyn);
             if (e == hipSuccess && sums)
                 e = launch_ne_steps(s, {part, 2 * cfg.P, (int)cfg.P, (int)k, c.a, c.b, norm_out, energy_out, st,
                                         nullptr, x.knorm, (int)cfg.P, check, st == 0});

@@ -286,6 +286,7 @@ struct ChainMultiCfg {
 };
 ChainMultiCfg chain_multi_config(int64_t n);
 size_t chain_multi_scratch_bytes(const ChainMultiCfg &cfg);
+bool chain_weights_in_lds(int64_t P, size_t wbytes, int64_t num_cus, size_t lds_per_cu);
 // device address of that run's timeout flag (int32) when it runs for c, else null
 int32_t *chain_multi_timeout(const Ctx &c);
 // check (host-visible, or null): as NeSteps::check; *checked: it was filled

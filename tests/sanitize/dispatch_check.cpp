@@ -1,0 +1,51 @@
+// Host-side check of the rules that choose a kernel or its launch shape.  Needs
+// no GPU; linked with the library's objects.  Exit status 0: every check passed.
+#include <cstdio>
+#include <string>
+
+#include "chebtd.h"
+#include "internal.h"
+
+using namespace chebtd;
+
+static int failures = 0;
+#define CHECK(cond)                                                                \
+    do {                                                                           \
+        if (!(cond)) {                                                             \
+            std::fprintf(stderr, "check failed: %s (line %d)\n", #cond, __LINE__); \
+            ++failures;                                                            \
+        }                                                                          \
+    } while (0)
+
+// Workgroups of the several-workgroup chain run wait on each other.  Counted
+// here: four runs at once, one per hardware queue, find room for every
+// workgroup on 256 CUs of 160 KiB LDS, whatever n and M.
+static void chain_residency()
+{
+    const size_t lds = 160 * 1024;
+    bool in_lds = false, in_memory = false;
+    for (int64_t n = 129; n <= 4096; n += n < 600 ? 1 : 37) {
+        const ChainMultiCfg cfg = chain_multi_config(n);
+        for (int M = 1; M <= 40000; M += 61) {
+            const size_t wbytes = (size_t)(M + 1) * sizeof(double);
+            if (wbytes + 1024 > lds) continue;  // never in LDS
+            const bool kept = chain_weights_in_lds(cfg.P, wbytes, 256, lds);
+            const size_t per_wg = (kept ? wbytes : 0) + 1024;
+            CHECK((int64_t)(lds / per_wg) * 256 >= 4 * cfg.P);
+            (kept ? in_lds : in_memory) = true;
+            if (failures > 20) return;
+        }
+    }
+    CHECK(in_lds && in_memory);
+    // the double well of 4096 points at dt = 0.5 (order 7256) keeps them in LDS
+    CHECK(chain_weights_in_lds(chain_multi_config(4096).P, 7257 * sizeof(double), 256, lds));
+}
+
+int main(int argc, char **argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "chain") chain_residency();
+    else CHECK(!"known check");
+    std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
+    return failures == 0 ? 0 : 1;
+}
