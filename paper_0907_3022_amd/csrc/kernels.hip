@@ -508,7 +508,8 @@ hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t 
 // A call's copy of a CSR matrix: real parts and columns, the entries of 64
 // rows ordered so that a wavefront's loads are contiguous (copy_slot; no
 // padding), 32-bit row starts, and a word that tells whether any imaginary
-// part is not zero (the orders then read the caller's arrays).  The caller's
+// part is not zero or a row does not fit (the orders then read the caller's
+// arrays).  The caller's
 // arrays are only borrowed and may hold other values at the next call, so the
 // copy is made anew in every call.
 //
@@ -528,6 +529,13 @@ __global__ __launch_bounds__(kBlock) void k_csr_copy(OpCsr op, int64_t nnz, doub
     const int64_t i = CsrRow::row(op);
     if (i < 0) return;
     const int64_t p0 = op.rowptr[i], p1 = op.rowptr[i + 1];
+    // the caller's row starts may have changed since they were checked: rows
+    // past the nnz entries there is room for leave the call to his arrays
+    const bool bad = p0 < 0 || p1 < p0 || p1 > nnz || (i == op.n - 1 && p1 != nnz);
+    if (__ballot(bad) != 0) {
+        if (bad) *mixed = 1;
+        return;
+    }
     const int32_t len = (int32_t)(p1 - p0);
     uint32_t p = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)p0);
     bool im = false;

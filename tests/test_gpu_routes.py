@@ -5,7 +5,7 @@ import pytest
 
 import oracle as O
 from test_gpu_deep import run
-from test_gpu_parity import assert_state_close, chain_case, dev, gpu_context, host, say
+from test_gpu_parity import _hermitian_csr, assert_state_close, chain_case, dev, gpu_context, host, say
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +63,45 @@ def test_chain_runs_on_four_streams(torch, cheb):
     for ctx, psi in zip(ctxs, psis):
         np.testing.assert_array_equal(host(psi), alone)
         ctx.close()
+
+
+# the arrays are borrowed: a matrix of more entries, written over them after it
+# was registered, is what the next call runs
+def test_csr_copy_stays_inside_its_room(torch, cheb, monkeypatch):
+    monkeypatch.setenv("CHEBTD_CSR_COPY", "1")
+    n = 300
+    rng = np.random.default_rng(3)
+
+    def matrix(fill):
+        A = np.diag(rng.standard_normal(n)).astype(np.complex128)
+        for i in range(0, n - fill, 2):
+            A[i, i + fill] = A[i + fill, i] = rng.standard_normal()
+        rowptr, cols, vals = _hermitian_csr(A)
+        return rowptr, cols.astype(np.int32), vals
+
+    small, large = matrix(n), matrix(7)
+    room = len(large[1])
+    assert len(small[1]) < room
+    r_d = dev(torch, small[0])
+    c_d = torch.zeros(room, dtype=torch.int32, device="cuda")
+    v_d = torch.zeros(room, dtype=torch.complex128, device="cuda")
+    c_d[:len(small[1])] = dev(torch, small[1])
+    v_d[:len(small[1])] = dev(torch, small[2])
+    psi0 = rng.standard_normal(n) + 1j * rng.standard_normal(n)
+    psi0 /= np.linalg.norm(psi0)
+    ctx = cheb.Context()
+    ctx.csr(r_d, c_d[:len(small[1])], v_d[:len(small[1])])
+    ctx.set_bounds(-12.0, 12.0)
+    ctx.plan_order(0.2, 12)
+    say("[gpu] csr arrays rewritten with more entries")
+    for rowptr, cols, vals in (small, large):
+        r_d.copy_(dev(torch, rowptr))
+        c_d[:len(cols)] = dev(torch, cols)
+        v_d[:len(cols)] = dev(torch, vals)
+        psi = dev(torch, psi0)
+        ctx.propagate(psi, 2, None, None, cheb.NO_CHECK)
+        torch.cuda.synchronize()
+        H = O.import_csr(rowptr, cols.astype(np.int64), vals)
+        ref, _, _ = O.propagate(H, O.Plan(-12.0, 12.0, 0.2, M=12), psi0, 2, want_obs=True)
+        assert_state_close(host(psi), ref)
+    ctx.close()
