@@ -433,7 +433,9 @@ int chebtd_adjoint_run(chebtd_ctx *ctx, int64_t run_id, double *gbar_dev, double
  * often after its head.  1 elsewhere; CHEBTD_SINGLE_ORDER in `flags` times
  * the one-order kernel.  The Holstein and CSR kernels are timed in the pattern a
  * step runs them: two launches without the accumulator for every one that
- * updates it with three orders.  Needs a plan.  Synchronises.
+ * updates it with three orders, a CSR matrix as a call of one step reads it
+ * (k_iter_csr<OpCsrCopy>: from the copy made for the call, which is not timed).
+ * Needs a plan.  Synchronises.
  * name_out and orders_out may be NULL. */
 int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, double *ms_per_launch,
                                  const char **name_out, int *orders_out);

@@ -299,6 +299,7 @@ hipError_t launch_fill_zero(hipStream_t s, double *p, int64_t count);
 size_t csr_copy_bytes(int64_t n, int64_t nnz);
 bool csr_copy_pays(const Ctx &c, int64_t orders);
 hipError_t launch_csr_copy(const Ctx &c, hipStream_t s);
+const int32_t *csr_copy_mixed(const Ctx &c);  // device word: not 0 if the copy does not hold the matrix
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,
                             int64_t nnz, int64_t *flag);
 

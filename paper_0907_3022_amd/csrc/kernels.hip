@@ -578,6 +578,8 @@ bool csr_copy_pays(const Ctx &c, int64_t orders)
     return orders >= kCsrCopyOrders && c.nnz >= kCsrCopyEntries;
 }
 
+const int32_t *csr_copy_mixed(const Ctx &c) { return make_csr_copy(c).mixed; }
+
 hipError_t launch_csr_copy(const Ctx &c, hipStream_t s)
 {
     const OpCsrCopy op = make_csr_copy(c);

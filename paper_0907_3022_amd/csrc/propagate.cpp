@@ -38,6 +38,12 @@ double2 weight(const Ctx *c, int k)
     return make_double2(c->gamma[2 * (size_t)k], c->gamma[2 * (size_t)k + 1]);
 }
 
+// The orders of one call read the matrix copy: until its end.
+struct CopyUse {
+    Ctx *c;
+    ~CopyUse() { c->csr_copy = false; }
+};
+
 // Orders of the multi-order pass a step runs most often after its head (ties:
 // the deeper), or the head's own when no such pass follows it.
 int dominant_pass(const Ctx &c)
@@ -410,10 +416,7 @@ int chebtd_propagate(chebtd_ctx *ctx, double *psi_dev, int64_t K, double *norm_d
     hipError_t e = hipSuccess;
 
     // a real CSR matrix: this call's orders read a copy of it
-    struct CopyUse {
-        Ctx *c;
-        ~CopyUse() { c->csr_copy = false; }
-    } copy_use{c};
+    CopyUse copy_use{c};
     if (csr_copy_pays(*c, K * (int64_t)std::max(c->M, 1))) {
         e = launch_csr_copy(*c, s);
         if (e != hipSuccess) return hip_fail(c, e, "matrix copy");
@@ -640,8 +643,9 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     const bool pairs = !pipe && c->use_pairs && !(flags & CHEBTD_SINGLE_ORDER);
     // the multi-order kernel the step spends most of its passes in
     const int dp = pairs ? dominant_pass(*c) : 2;
-    static const char *names[] = {"k_iter_chain", "k_iter_honey<0>", "k_iter_honey<1>", "k_iter_csr",
-                                  "k_pair<0,false>", "k_pair<1,false>", "k_iter_hol<true, false>", "k_iter_hol<false, false>"};
+    static const char *names[] = {"k_iter_chain", "k_iter_honey<0>", "k_iter_honey<1>", "k_iter_csr<OpCsr>",
+                                  "k_pair<0,false>", "k_pair<1,false>", "k_iter_hol<true, false>", "k_iter_hol<false, false>",
+                                  "k_iter_csr<OpCsrCopy>"};
     // [edge][streaming stores][orders per pass]
     static const char *deep_names[2][2][kMaxDepth + 1] = {
         {{"", "", "", "k_deep<0,3,false,false>", "k_deep<0,4,false,false>", "k_deep<0,5,false,false>",
@@ -653,10 +657,20 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
          {"", "", "", "k_deep<1,3,false,true>", "k_deep<1,4,false,true>", "k_deep<1,5,false,true>",
           "k_deep<1,6,false,true>"}}};
     const bool arm = c->kind == HKind::Honeycomb && c->edge == CHEBTD_ARMCHAIR;
+    CopyUse copy_use{c};
+    if (csr_copy_pays(*c, c->M)) {  // as a call of one step
+        hipError_t e = launch_csr_copy(*c, c->stream);
+        int32_t *mixed = reinterpret_cast<int32_t *>(c->pinned);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(mixed, csr_copy_mixed(*c), sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return hip_fail(c, e, "matrix copy");
+        c->csr_copy = *mixed == 0;
+    }
     const char *nm = (pairs && dp > 2) ? deep_names[arm ? 1 : 0][deep_stream_stores(*c) ? 1 : 0][dp]
                      : pairs ? (arm ? names[5] : names[4])
                      : c->kind == HKind::Chain    ? names[0]
-                     : c->kind == HKind::Csr      ? names[3]
+                     : c->kind == HKind::Csr      ? names[c->csr_copy ? 8 : 3]
                      : c->kind == HKind::Holstein ? names[c->hol_brows > 0 ? 6 : 7]
                      : (c->edge == CHEBTD_ZIGZAG ? names[1] : names[2]);
     int npass = 1, orders = pairs ? dp : 1;

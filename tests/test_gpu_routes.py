@@ -105,3 +105,29 @@ def test_csr_copy_stays_inside_its_room(torch, cheb, monkeypatch):
         ref, _, _ = O.propagate(H, O.Plan(-12.0, 12.0, 0.2, M=12), psi0, 2, want_obs=True)
         assert_state_close(host(psi), ref)
     ctx.close()
+
+
+def tridiagonal(n, off):
+    """rowptr, col, val of a Hermitian tridiagonal matrix."""
+    i = np.arange(n)
+    col = i[:, None] + np.array([-1, 0, 1])
+    val = np.broadcast_to(np.array([np.conj(off), 0.5, off]), col.shape)
+    keep = (col >= 0) & (col < n)
+    rowptr = np.concatenate([[0], np.cumsum(keep.sum(1))]).astype(np.int64)
+    return rowptr, col[keep].astype(np.int32), val[keep].astype(np.complex128)
+
+
+# the timed CSR kernel is the one that a call of one step runs
+@pytest.mark.parametrize("off,M,name", [(0.3, 12, "k_iter_csr<OpCsrCopy>"), (0.3, 5, "k_iter_csr<OpCsr>"),
+                                        (0.3 + 0.1j, 12, "k_iter_csr<OpCsr>")])
+def test_csr_timing_names_the_kernel_that_runs(torch, cheb, off, M, name):
+    n = 360000
+    arrays = [dev(torch, a) for a in tridiagonal(n, off)]
+    assert arrays[1].numel() > 1 << 20
+    ctx = cheb.Context()
+    ctx.csr(*arrays)
+    ctx.set_bounds(-2.0, 2.0)
+    ctx.plan_order(0.5, M)
+    ms, got, orders = ctx.time_recursion_kernel(3)
+    ctx.close()
+    assert got == name and orders == 1 and ms > 0
