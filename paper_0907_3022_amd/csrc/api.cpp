@@ -350,6 +350,7 @@ int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_
     c->rowptr = rowptr_dev;
     c->col = col_dev;
     c->val = val_dev;
+    *csr_seen(*c) = 0;
     // Room for the copies of many-order calls (launch_csr_copy), if it is a
     // small part of what is left on the device; without it the orders read
     // the caller's arrays.

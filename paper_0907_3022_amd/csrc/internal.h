@@ -123,6 +123,8 @@ struct Ctx {
     const double *val = nullptr;
     DevBuf csr_buf;         // room for a call's copy (mixed word, real parts, columns, row starts); may be empty
     bool csr_copy = false;  // this call's orders read the copy
+    bool csr_look = false;  // and tells the host whether the matrix is real
+    unsigned csr_calls = 0;
     // Holstein (owned device copies)
     bool holstein = false;
     int hol_L = 0, hol_nph = 0;
@@ -180,7 +182,7 @@ struct Ctx {
     DevBuf results;    // double[16], then kStepSumBytes of per-step partial sums
     DevBuf counter;    // int64[4]
     DevBuf chainx;     // exchange strips, flags and partials of the several-workgroup chain run
-    double *pinned = nullptr;  // host pinned double[16]
+    double *pinned = nullptr;  // host pinned double[16]: checks from 0, time-out at 8, csr_seen at 12
     double check_tol = 1e-6;
     int64_t plan_version = 0;  // bumped by every plan
     int64_t run_seq = 0;       // numbers the checkpointing propagation runs
@@ -297,7 +299,10 @@ hipError_t launch_fill_zero(hipStream_t s, double *p, int64_t count);
 // instead of the caller's arrays, whether a call of `orders` orders makes it,
 // and making it
 size_t csr_copy_bytes(int64_t n, int64_t nnz);
-bool csr_copy_pays(const Ctx &c, int64_t orders);
+bool csr_copy_pays(Ctx &c, int64_t orders);
+// host word (pinned): 1 if the matrix that a call looked at last was real, 2 if
+// not, 0: none did
+inline int32_t *csr_seen(const Ctx &c) { return reinterpret_cast<int32_t *>(c.pinned + 12); }
 hipError_t launch_csr_copy(const Ctx &c, hipStream_t s);
 const int32_t *csr_copy_mixed(const Ctx &c);  // device word: not 0 if the copy does not hold the matrix
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,

@@ -41,10 +41,37 @@ static void chain_residency()
     CHECK(chain_weights_in_lds(chain_multi_config(4096).P, 7257 * sizeof(double), 256, lds));
 }
 
+// A matrix found complex is not copied again, but looked at now and then.
+static void csr_copies()
+{
+    double pinned[16] = {};
+    char room = 0;
+    Ctx c;
+    c.pinned = pinned;
+    c.kind = HKind::Csr;
+    c.n = 300000;
+    c.nnz = 1200000;
+    c.csr_buf.p = &room;  // never dereferenced here
+    c.csr_buf.bytes = csr_copy_bytes(c.n, c.nnz);
+    CHECK(csr_copy_pays(c, 8) && csr_copy_pays(c, 8) && !csr_copy_pays(c, 7));
+    *csr_seen(c) = 1;
+    for (int call = 0; call < 40; ++call) CHECK(csr_copy_pays(c, 8));
+    *csr_seen(c) = 2;
+    int looked = 0;
+    for (int call = 0; call < 160; ++call)
+        if (csr_copy_pays(c, 8)) {
+            ++looked;
+            CHECK(c.csr_look);
+        }
+    CHECK(looked >= 5 && looked <= 16);
+    c.csr_buf.p = nullptr;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "chain") chain_residency();
+    else if (what == "csr") csr_copies();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;
