@@ -332,14 +332,15 @@ int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_
         return fail(c, CHEBTD_E_ARG, "chebtd_h_csr: n must fit int32 column indices");
     // reject malformed structure here: the kernels index v with these columns
     int64_t *flag = static_cast<int64_t *>(c->counter.p) + 1;
-    hipError_t e = launch_csr_check(c->stream, rowptr_dev, col_dev, n, nnz, flag);
+    hipError_t e = launch_csr_check(c->stream, rowptr_dev, col_dev, n, nnz, flag,
+                                    static_cast<double *>(c->results.p) + 16);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(c->pinned, flag, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream);
+        e = hipMemcpyAsync(c->pinned, flag, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_h_csr structure check");
-    int64_t bad = 0;
-    std::memcpy(&bad, c->pinned, sizeof(int64_t));
-    if (bad)
+    int64_t seen[3] = {};  // malformed, and the rows' shape
+    std::memcpy(seen, c->pinned, sizeof seen);
+    if (seen[0])
         return fail(c, CHEBTD_E_ARG,
                     "chebtd_h_csr: rowptr must run from 0 to nnz without decreasing and every column "
                     "must lie in [0, n)");
@@ -351,11 +352,13 @@ int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_
     c->col = col_dev;
     c->val = val_dev;
     *csr_seen(*c) = 0;
+    c->csr_orders = csr_copy_orders(n, nnz, seen[1], seen[2]);
     // Room for the copies of many-order calls (launch_csr_copy), if it is a
     // small part of what is left on the device; without it the orders read
     // the caller's arrays.
     size_t left = 0, total = 0;
-    const size_t need = csr_copy_bytes(n, nnz);
+    const bool pays = c->csr_orders != INT64_MAX || std::getenv("CHEBTD_CSR_COPY");
+    const size_t need = pays ? csr_copy_bytes(n, nnz) : 0;
     if (c->csr_buf.bytes < need || c->csr_buf.bytes / 2 > need) release(c->csr_buf);
     if (need && !c->csr_buf.p && hipMemGetInfo(&left, &total) == hipSuccess && need <= left / 8) {
         if (hipMalloc(&c->csr_buf.p, need) == hipSuccess)

@@ -125,6 +125,7 @@ struct Ctx {
     bool csr_copy = false;  // this call's orders read the copy
     bool csr_look = false;  // and tells the host whether the matrix is real
     unsigned csr_calls = 0;
+    int64_t csr_orders = INT64_MAX;  // fewest orders of a call that make it (csr_copy_orders)
     // Holstein (owned device copies)
     bool holstein = false;
     int hol_L = 0, hol_nph = 0;
@@ -300,13 +301,17 @@ hipError_t launch_fill_zero(hipStream_t s, double *p, int64_t count);
 // and making it
 size_t csr_copy_bytes(int64_t n, int64_t nnz);
 bool csr_copy_pays(Ctx &c, int64_t orders);
+// from the sum over wavefronts of 64 times their longest row, and the longest row
+int64_t csr_copy_orders(int64_t n, int64_t nnz, int64_t padded, int64_t longest);
 // host word (pinned): 1 if the matrix that a call looked at last was real, 2 if
 // not, 0: none did
 inline int32_t *csr_seen(const Ctx &c) { return reinterpret_cast<int32_t *>(c.pinned + 12); }
 hipError_t launch_csr_copy(const Ctx &c, hipStream_t s);
 const int32_t *csr_copy_mixed(const Ctx &c);  // device word: not 0 if the copy does not hold the matrix
+// flag[0]: not 0 if malformed; flag[1], flag[2]: csr_copy_orders' padded and
+// longest; scratch: the context's step sums
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,
-                            int64_t nnz, int64_t *flag);
+                            int64_t nnz, int64_t *flag, double *scratch);
 
 // adjoint kernels (adjoint.hip)
 hipError_t launch_recompute(const Ctx &c, hipStream_t s, const double2 *vk, const double2 *vkm1,

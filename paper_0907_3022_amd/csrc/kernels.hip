@@ -474,33 +474,76 @@ __global__ __launch_bounds__(kBlock) void k_scale_copy(const double2 *src, doubl
 // column index falls outside [0, n).  Columns are read only inside a row
 // whose bounds were verified first.
 // ---------------------------------------------------------------------------
+constexpr int kShapeSlots = 64;  // lines over which blocks spread their counts (11 ns each on one line)
+
 __global__ __launch_bounds__(kBlock) void k_csr_check(const int64_t *__restrict__ rowptr,
                                                       const int32_t *__restrict__ col, int64_t n,
-                                                      int64_t nnz, int64_t *flag)
+                                                      int64_t nnz, int64_t *flag, unsigned long long *shape)
 {
+    __shared__ unsigned long long most[kBlock / 64];
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t p0 = rowptr[i], p1 = rowptr[i + 1];
-    bool bad = p0 < 0 || p1 < p0 || p1 > nnz;
-    if (i == 0 && p0 != 0) bad = true;
-    if (i == n - 1 && p1 != nnz) bad = true;
-    if (!bad) {
-        for (int64_t p = p0; p < p1; ++p) {
-            const int32_t c = col[p];
-            if (c < 0 || (int64_t)c >= n) bad = true;
+    int64_t len = 0;
+    if (i < n) {
+        const int64_t p0 = rowptr[i], p1 = rowptr[i + 1];
+        bool bad = p0 < 0 || p1 < p0 || p1 > nnz;
+        if (i == 0 && p0 != 0) bad = true;
+        if (i == n - 1 && p1 != nnz) bad = true;
+        if (!bad) {
+            len = p1 - p0;
+            for (int64_t p = p0; p < p1; ++p) {
+                const int32_t c = col[p];
+                if (c < 0 || (int64_t)c >= n) bad = true;
+            }
         }
+        if (bad) flag[0] = 1;
     }
-    if (bad) flag[0] = 1;
+    // the longest row of each wavefront
+    long long longest = len;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) longest = max(longest, __shfl_xor(longest, o, 64));
+    if ((threadIdx.x & 63) == 0) most[threadIdx.x >> 6] = (unsigned long long)longest;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long sum = 0, top = 0;
+        for (unsigned long long m : most) {
+            sum += 64 * m;
+            top = max(top, m);
+        }
+        shape += (blockIdx.x % kShapeSlots) * 8;
+        atomicAdd(&shape[0], sum);
+        atomicMax(&shape[1], top);
+    }
 }
 
-__global__ void k_clear_flag(int64_t *flag) { flag[0] = 0; }
+__global__ void k_clear_shape(int64_t *flag, unsigned long long *shape)
+{
+    if (threadIdx.x == 0) flag[0] = 0;
+    shape[8 * threadIdx.x] = shape[8 * threadIdx.x + 1] = 0;
+}
+
+__global__ void k_csr_shape(int64_t *flag, const unsigned long long *shape)
+{
+    long long sum = (long long)shape[8 * threadIdx.x], top = (long long)shape[8 * threadIdx.x + 1];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        sum += __shfl_xor(sum, o, 64);
+        top = max(top, __shfl_xor(top, o, 64));
+    }
+    if (threadIdx.x == 0) {
+        flag[1] = sum;
+        flag[2] = top;
+    }
+}
 
 hipError_t launch_csr_check(hipStream_t s, const int64_t *rowptr, const int32_t *col, int64_t n,
-                            int64_t nnz, int64_t *flag)
+                            int64_t nnz, int64_t *flag, double *scratch)
 {
-    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, s, flag);
+    static_assert(kShapeSlots == 64 && kShapeSlots * 64 <= kStepSumBytes, "one wavefront sums the slots");
+    unsigned long long *shape = reinterpret_cast<unsigned long long *>(scratch);
+    hipLaunchKernelGGL(k_clear_shape, dim3(1), dim3(kShapeSlots), 0, s, flag, shape);
     const int64_t nb = (n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_csr_check, dim3((unsigned)nb), dim3(kBlock), 0, s, rowptr, col, n, nnz, flag);
+    hipLaunchKernelGGL(k_csr_check, dim3((unsigned)nb), dim3(kBlock), 0, s, rowptr, col, n, nnz, flag, shape);
+    hipLaunchKernelGGL(k_csr_shape, dim3(1), dim3(kShapeSlots), 0, s, flag, shape);
     return hipGetLastError();
 }
 
@@ -562,7 +605,14 @@ __global__ void k_csr_tell(const int32_t *mixed, int32_t *seen) { *seen = *mixed
 // From eight orders and 2^20 entries on: 64 / 8 / 4 orders of a call take the
 // copy at 1.75M entries 1.28 / 1.09 / 0.96 times as fast as without it, at
 // 7.4M 1.31 / 1.13 / 0.98, at 64M 1.31 / 1.12 / 0.97; at 0.41M entries, which
-// the L2 caches hold, 0.97 / 0.87 / 0.81.
+// the L2 caches hold, 0.97 / 0.87 / 0.81.  Those rows are even.  A wavefront
+// walks the copy to the end of its longest row together: with rows of 4 entries
+// and one of 16 / 32 / 128 in each 64 (columns near the row) 64 orders run 1.04
+// / 0.94 / 0.87 times as fast, with lengths from 0 to 8 1.44.  And copying a
+// row entry after entry takes longer the longer it is: 512 / 1024 / 2048
+// entries in every row 0.91 / 0.88 / 0.85 with 8 orders, 1.12 / 1.07 / 1.03 with
+// 64; so does one row of 100 among rows of 8 (0.92, 1.21), and rows of a
+// single entry gain little (0.97, 1.03).
 constexpr int64_t kCsrCopyOrders = 8, kCsrCopyEntries = 1 << 20;
 
 size_t csr_copy_bytes(int64_t n, int64_t nnz)
@@ -571,14 +621,22 @@ size_t csr_copy_bytes(int64_t n, int64_t nnz)
     return 16 + (size_t)nnz * 12 + (size_t)(n + 1) * 4;
 }
 
+constexpr int64_t kCsrCopyOrdersLong = 64, kCsrLongRow = 256;
 constexpr int kCsrLook = 16;
+
+int64_t csr_copy_orders(int64_t n, int64_t nnz, int64_t padded, int64_t longest)
+{
+    if (2 * padded > 5 * nnz || longest * n > 16 * nnz) return INT64_MAX;  // uneven
+    const bool short_rows = longest <= kCsrLongRow && longest * n <= 8 * nnz;
+    return short_rows && nnz >= 2 * n ? kCsrCopyOrders : kCsrCopyOrdersLong;
+}
 
 bool csr_copy_pays(Ctx &c, int64_t orders)
 {
     const size_t need = csr_copy_bytes(c.n, c.nnz);
     if (c.kind != HKind::Csr || need == 0 || c.csr_buf.bytes < need) return false;
     if (const char *env = std::getenv("CHEBTD_CSR_COPY")) return std::atoi(env) != 0;
-    if (orders < kCsrCopyOrders || c.nnz < kCsrCopyEntries) return false;
+    if (orders < c.csr_orders || c.nnz < kCsrCopyEntries) return false;
     const int32_t seen = *static_cast<volatile int32_t *>(csr_seen(c));
     c.csr_look = seen == 0 || ++c.csr_calls % kCsrLook == 0;
     return seen != 2 || c.csr_look;

@@ -53,6 +53,7 @@ static void csr_copies()
     c.nnz = 1200000;
     c.csr_buf.p = &room;  // never dereferenced here
     c.csr_buf.bytes = csr_copy_bytes(c.n, c.nnz);
+    c.csr_orders = csr_copy_orders(c.n, c.nnz, 64 * 4 * ((c.n + 63) / 64), 4);
     CHECK(csr_copy_pays(c, 8) && csr_copy_pays(c, 8) && !csr_copy_pays(c, 7));
     *csr_seen(c) = 1;
     for (int call = 0; call < 40; ++call) CHECK(csr_copy_pays(c, 8));
@@ -65,6 +66,13 @@ static void csr_copies()
         }
     CHECK(looked >= 5 && looked <= 16);
     c.csr_buf.p = nullptr;
+    // even rows; lengths of 0 to 8; one long row in every 64, in all; long rows
+    const int64_t n = 1 << 20, never = INT64_MAX;
+    CHECK(csr_copy_orders(n, 4 * n, 4 * n, 4) == 8 && csr_copy_orders(n, 4 * n, 8 * n, 8) == 8);
+    CHECK(csr_copy_orders(n, 5 * n, 64 * n, 64) == never);
+    CHECK(csr_copy_orders(n, 3 * n, 3 * n + 64 * n, n) == never && csr_copy_orders(n, 5 * n, 6 * n, n) == never);
+    CHECK(csr_copy_orders(2048, 2048 * 2048, 2048 * 2048, 2048) == 64);
+    CHECK(csr_copy_orders(n, n, n, 1) == 64);
 }
 
 int main(int argc, char **argv)

@@ -131,3 +131,26 @@ def test_csr_timing_names_the_kernel_that_runs(torch, cheb, off, M, name):
     ms, got, orders = ctx.time_recursion_kernel(3)
     ctx.close()
     assert got == name and orders == 1 and ms > 0
+
+
+# the rows' shape that the rule above counts on, found when the matrix is
+# registered: one long row in every wavefront's 64 and the copy does not pay
+@pytest.mark.parametrize("every,copied", [(0, True), (64, False), (360000, False)])
+def test_csr_uneven_rows_are_not_copied(torch, cheb, every, copied):
+    n = 360000
+    rowptr, col, val = tridiagonal(n, 0.3)
+    cnt = np.diff(rowptr)
+    if every:
+        cnt[::every] += 200
+        rng = np.random.default_rng(1)
+        col = rng.integers(0, n, int(cnt.sum())).astype(np.int32)
+        val = np.zeros(col.size, dtype=np.complex128)
+        rowptr = np.concatenate([[0], np.cumsum(cnt)]).astype(np.int64)
+    ctx = cheb.Context()
+    arrays = [dev(torch, a) for a in (rowptr, col, val)]
+    ctx.csr(*arrays)
+    ctx.set_bounds(-2.0, 2.0)
+    ctx.plan_order(0.5, 80)
+    _, name, _ = ctx.time_recursion_kernel(2)
+    ctx.close()
+    assert ("Copy" in name) == copied
