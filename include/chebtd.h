@@ -113,7 +113,8 @@ int chebtd_h_honeycomb(chebtd_ctx *ctx, int64_t width, int64_t length, int edge,
  * describe a Hermitian matrix; that is not checked.  From 2^20 entries on
  * this takes room on the device for matrices of even rows (12 B an entry, 4 B a
  * row, if that is at most an eighth of what is free) in which calls of eight
- * orders or more (64 with rows past 256 entries) put a copy of a real matrix. */
+ * orders or more (64 with rows past 256 entries) put a copy of a real matrix.
+ * An allocation of the context that fails gives the room back and tries again. */
 int chebtd_h_csr(chebtd_ctx *ctx, int64_t n, int64_t nnz, const int64_t *rowptr_dev,
                  const int32_t *col_dev, const double *val_dev);
 

@@ -51,6 +51,11 @@ int ensure(Ctx *c, DevBuf &b, size_t bytes, const char *what)
     release(b);
     if (bytes == 0) return CHEBTD_OK;
     hipError_t e = hipMalloc(&b.p, bytes);
+    if (e != hipSuccess && c->csr_buf.p && !c->csr_copy) {  // the matrix copy's room is optional
+        (void)hipGetLastError();
+        release(c->csr_buf);
+        e = hipMalloc(&b.p, bytes);
+    }
     if (e != hipSuccess) {
         b.p = nullptr;
         (void)hipGetLastError();

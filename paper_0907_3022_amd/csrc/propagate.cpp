@@ -657,6 +657,11 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
          {"", "", "", "k_deep<1,3,false,true>", "k_deep<1,4,false,true>", "k_deep<1,5,false,true>",
           "k_deep<1,6,false,true>"}}};
     const bool arm = c->kind == HKind::Honeycomb && c->edge == CHEBTD_ARMCHAIR;
+    // scratch: four vectors and an accumulator, zeroed
+    DevBuf scratch;
+    const size_t vb = (size_t)c->n * sizeof(double2);
+    int rc = ensure(c, scratch, 5 * vb, "timing vectors");
+    if (rc) return rc;
     CopyUse copy_use{c};
     if (csr_copy_pays(*c, c->M)) {  // as a call of one step
         hipError_t e = launch_csr_copy(*c, c->stream);
@@ -664,7 +669,10 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
         if (e == hipSuccess)
             e = hipMemcpyAsync(mixed, csr_copy_mixed(*c), sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "matrix copy");
+        if (e != hipSuccess) {
+            release(scratch);
+            return hip_fail(c, e, "matrix copy");
+        }
         c->csr_copy = *mixed == 0;
     }
     const char *nm = (pairs && dp > 2) ? deep_names[arm ? 1 : 0][deep_stream_stores(*c) ? 1 : 0][dp]
@@ -680,11 +688,6 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     }
     if (name_out) *name_out = nm;
     if (orders_out) *orders_out = orders;
-    // scratch: four vectors and an accumulator, zeroed
-    DevBuf scratch;
-    const size_t vb = (size_t)c->n * sizeof(double2);
-    int rc = ensure(c, scratch, 5 * vb, "timing vectors");
-    if (rc) return rc;
     hipStream_t s = c->stream;
     double2 *V0 = static_cast<double2 *>(scratch.p), *V1 = V0 + c->n, *V2 = V1 + c->n, *V3 = V2 + c->n,
             *acc = V3 + c->n;

@@ -8,6 +8,10 @@
 
 using namespace chebtd;
 
+namespace chebtd {
+int ensure(Ctx *c, DevBuf &b, size_t bytes, const char *what);  // api.cpp
+}
+
 static int failures = 0;
 #define CHECK(cond)                                                                \
     do {                                                                           \
@@ -75,11 +79,27 @@ static void csr_copies()
     CHECK(csr_copy_orders(n, n, n, 1) == 64);
 }
 
+// An allocation that fails (there is no device here) gives the room of the
+// matrix copy back, unless a call is reading the copy.
+static void room_given_back()
+{
+    char room = 0;
+    Ctx c;
+    DevBuf b;
+    c.csr_buf.p = &room;  // not an allocation: freeing it is refused
+    c.csr_buf.bytes = 1;
+    c.csr_copy = true;
+    CHECK(ensure(&c, b, size_t(1) << 50, "test") == CHEBTD_E_OOM && c.csr_buf.p != nullptr);
+    c.csr_copy = false;
+    CHECK(ensure(&c, b, size_t(1) << 50, "test") == CHEBTD_E_OOM && c.csr_buf.p == nullptr && b.p == nullptr);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "chain") chain_residency();
     else if (what == "csr") csr_copies();
+    else if (what == "room") room_given_back();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;
