@@ -199,6 +199,56 @@ std::vector<int> plan_passes(const Ctx &c, int M)
     return out;
 }
 
+// Blocks of the head pass of `passes`.
+int64_t walk_head_blocks(const Ctx &c)
+{
+    const int h = c.passes[0];
+    return h > 2 ? deep_grid_blocks(c, c.deep_rows[h], h) : pair_grid_blocks(c, c.pair_rows);
+}
+
+// Steps that single-wavefront passes run in less time.  A pipelined pass costs
+// what eight orders do whatever M is, and a tiled one loads and publishes W
+// rows first, while M <= 6 takes one walk of 40 B per site (M = 2: 72 B, which
+// ends its lead where the vectors leave the last-level cache).  Walked time over
+// pipelined or tiled, measured on MI355X over four steps (in brackets: with
+// norms, energies and the check, which costs a walked run a kernel more):
+//   more than 48 rows, M = 2 / 3 / 5 / 6: 0.39 / 0.43 / 0.67 / 0.81 (0.53 / 0.58
+//   / 0.78 / 0.89) at 64 x 1000, 0.61 / 0.53 / 0.71 / 1.03 (0.73 / 0.68 / 0.83 /
+//   1.10) at 128 x 8192, 1.37 / 0.62 / 0.94 / 1.11 (1.51 / 0.75 / 0.98 / 1.18) at
+//   500 x 8000, 1.19 / 0.65 / 0.67 / 0.80 (1.25 / 0.74 / 0.75 / 0.86) at 1024 x 8192;
+//   33 to 48 rows, M = 2 / 3 / 4 / 5: 0.55 / 0.62 / 0.87 / 0.84 at 40 x 500, 0.80 /
+//   0.77 / 1.06 / 1.00 at 40 x 10000, 1.28 / 0.72 / 0.99 / 0.86 at 40 x 40000, 1.79 /
+//   0.64 / 0.86 / 0.83 at 40 x 120000; M = 6 above 0.94;
+//   17 to 32 rows, M = 2 / 3: 0.74 / 0.87 at 32 x 500, 1.08 / 1.08 at 32 x 8000,
+//   1.70 / 0.75 at 32 x 100000; up to 16 rows, and M >= 4, above 1;
+//   a third of a strip's columns or fewer (one strip, mostly idle lanes), two
+//   passes of five orders (M = 9, 10): 0.88 at 3000 x 16, 0.68 at 30000 x 16, where
+//   M = 11 / 15 / 25 take 0.89 / 0.87 / 0.78; 1.12 at 3000 x 60.
+bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled)
+{
+    const int64_t n = W * L, Ki = 1 << 10, Mi = 1 << 20;
+    if (!tiled) {
+        if (M == 2) return n < 5 * Mi / 2;
+        if (M == 3) return true;
+        if (M == 4 || M == 5) return n < 3 * Mi || n >= 6 * Mi;
+        if (M == 6) return (n <= 40 * Ki && W <= Ki) || n >= 6 * Mi;
+        if (L > 40) return false;
+        if (M == 9 || M == 10) return true;
+        return W >= 8 * Ki && L >= 8 && (M == 11 || M == 15 || M == 25);
+    }
+    if (W > 32) {
+        if (M == 2) return n <= 300 * Ki;
+        if (M == 3) return n <= 400 * Ki || n >= 3 * Mi / 2;
+        if (M == 4) return n <= 200 * Ki || n >= 4 * Mi;
+        return M == 5 && (n <= 128 * Ki || n >= 3 * Mi / 2);
+    }
+    if (W > 16) {
+        if (M == 2) return n <= 64 * Ki;
+        return M == 3 && ((W > 24 && n <= 64 * Ki) || n >= 7 * Mi / 4);
+    }
+    return false;
+}
+
 void invalidate_h(Ctx *c, bool csr = false)
 {
     if (!csr) release(c->csr_buf);
@@ -547,6 +597,17 @@ static int plan_common(Ctx *c, double dt, int M)
     hipError_t e = hipMemcpy(c->gamma_dev.p, up.data(), up.size() * sizeof(double), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(c, e, "chebtd_plan upload");
     const size_t vbytes = (size_t)c->n * 2 * sizeof(double);
+    // two more vectors let brick-wall Hamiltonians advance two orders per pass
+    c->use_pairs = false;
+    c->passes.clear();
+    c->pair_rows = choose_pair_rows(*c);
+    if (pair_supported(*c) && M >= 2) {
+        if ((rc = ensure(c, c->vC, vbytes, "work vector C")) || (rc = ensure(c, c->vD, vbytes, "work vector D")))
+            return rc;
+        c->use_pairs = true;
+        c->passes = plan_passes(*c, M);
+        for (int d = 3; d <= kMaxDepth; ++d) c->deep_rows[d] = choose_deep_rows(*c, d);
+    }
     // pipelined or tiled steps: the head partials of up to 32 steps, then a
     // norm partial per block of the last pass, in the context's step sums, or
     // for lattices of very many blocks two steps' behind vB
@@ -562,18 +623,28 @@ static int plan_common(Ctx *c, double dt, int M)
             pipe_time(c->W, c->L, c->pipe, c->num_cus) < us)
             c->tile.R = 0;
     }
+    c->walk = false;
+    if (c->kind == HKind::Honeycomb && c->use_pairs && (c->tile.R || !c->pipe.empty())) {
+        bool forced = false;  // a shape to run in any case
+        for (const char *v : {"CHEBTD_PIPE", "CHEBTD_PIPE_CHUNKS", "CHEBTD_TILE"}) forced = forced || std::getenv(v);
+        if (const char *env = std::getenv("CHEBTD_WALK"))
+            c->walk = std::atoi(env) != 0;
+        else
+            c->walk = !forced && walk_takes_step(c->W, c->L, M, c->tile.R != 0);
+        if (c->walk) c->tile.R = 0;
+    }
     size_t sums = 0;
     if (!c->pipe.empty() || c->tile.R) {
+        // of any plan's first (last) pass
         auto blocks = [&](bool last) -> int64_t {
-            if (!c->tile.R) {
-                // either plan's first (last) pass
-                int64_t nb = pipe_blocks(*c, last ? c->pipe.back() : c->pipe.front());
-                if (!c->pipe_ends.empty())
-                    nb = std::max(nb, pipe_blocks(*c, last ? c->pipe_ends.back() : c->pipe_ends.front()));
-                return nb;
+            if (c->tile.R) {
+                const int D = last ? c->tile.depths.back() : c->tile.depths.front();
+                return c->kind == HKind::Chain ? tile_blocks(*c, c->tile.R, D) : ribbon_tile_blocks(c->L, D);
             }
-            const int D = last ? c->tile.depths.back() : c->tile.depths.front();
-            return c->kind == HKind::Chain ? tile_blocks(*c, c->tile.R, D) : ribbon_tile_blocks(c->L, D);
+            int64_t nb = c->walk ? (last ? 2 * reduce_blocks(c->n) : walk_head_blocks(*c)) : 0;
+            for (const auto *p : {&c->pipe, &c->pipe_ends})
+                if (!p->empty()) nb = std::max(nb, pipe_blocks(*c, last ? p->back() : p->front()));
+            return nb;
         };
         const int64_t nb = blocks(false), nl = blocks(true);
         c->pipe_part = 2 * nb;
@@ -588,17 +659,6 @@ static int plan_common(Ctx *c, double dt, int M)
         return rc;
     c->pipe_sums = sums ? reinterpret_cast<double *>(static_cast<char *>(c->vB.p) + vbytes)
                         : static_cast<double *>(c->results.p) + 16;
-    // two more vectors let brick-wall Hamiltonians advance two orders per pass
-    c->use_pairs = false;
-    c->passes.clear();
-    c->pair_rows = choose_pair_rows(*c);
-    if (pair_supported(*c) && M >= 2) {
-        if ((rc = ensure(c, c->vC, vbytes, "work vector C")) || (rc = ensure(c, c->vD, vbytes, "work vector D")))
-            return rc;
-        c->use_pairs = true;
-        c->passes = plan_passes(*c, M);
-        for (int d = 3; d <= kMaxDepth; ++d) c->deep_rows[d] = choose_deep_rows(*c, d);
-    }
     if ((rc = ensure_partials(c))) return rc;
     if (c->kind == HKind::Chain) {
         const size_t xb = chain_multi_scratch_bytes(chain_multi_config(c->n));

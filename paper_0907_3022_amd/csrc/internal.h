@@ -175,6 +175,7 @@ struct Ctx {
     std::vector<PipeShape> pipe_ends;
     int pipe_rest = 0;
     TilePlan tile;           // tiled passes of chains and narrow ribbons
+    bool walk = false;       // steps without step-end pairs run `passes` all the same (walk_takes_step)
     int pipe_ring = 0;       // steps whose head partials are in flight
     int64_t pipe_part = 0;   // doubles per step of them
     double *pipe_sums = nullptr;  // [pipe_ring][pipe_part], then the last pass's norm partials
@@ -207,6 +208,10 @@ void step_weights(double a, double b, double dt, int M, std::vector<double> &gam
 // and as real factors: gamma_k = phase (-i)^k r_k
 void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma, std::vector<double> &r,
                   double2 *phase);
+// Whether a ribbon's step of M orders takes less time in single-wavefront passes
+// than pipelined or (tiled) in registers, and the blocks of such a step's head.
+bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled);
+int64_t walk_head_blocks(const Ctx &c);
 void shift_scale(double emin, double emax, double alpha, double *a, double *b);
 
 struct HolsteinCsr {

@@ -68,12 +68,13 @@ int dominant_pass(const Ctx &c)
 // any, comes last.  Pass outputs alternate between (vA, vC) and (vD, cur):
 // cur is free once the head pass has read it.
 // ends (or null): 2 n values that receive v_{M-1}, v_M of the step
+// partials: the head's norm and energy partials (finished here into norm_out
+// and energy_out where given)
 hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double2 *ends,
-                              double *norm_out, double *energy_out)
+                              double *partials, double *norm_out, double *energy_out)
 {
     double2 *A = static_cast<double2 *>(c->vA.p), *C = static_cast<double2 *>(c->vC.p),
             *D = static_cast<double2 *>(c->vD.p);
-    double *partials = static_cast<double *>(c->partials.p);
     const std::vector<int> &P = c->passes;
     const int h = P[0];
     double2 g[kMaxDepth + 1];
@@ -139,16 +140,18 @@ hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt,
     return k == c->M ? hipSuccess : hipErrorInvalidValue;
 }
 
-// Whether the steps run as pipelined or tiled passes.  ends: the step-end
-// pairs are wanted, which a padded last pipelined pass does not form.
+// Whether run_pipe runs the steps, as pipelined or tiled passes or as the
+// single-wavefront ones (Ctx::walk).  ends: the step-end pairs are wanted, which
+// a padded last pipelined pass does not form.
 bool use_pipe(const Ctx &c, unsigned flags, bool ends)
 {
-    return (c.tile.R || !(ends ? c.pipe_ends : c.pipe).empty()) && !(flags & CHEBTD_SINGLE_ORDER);
+    return (c.tile.R || (c.walk && !ends) || !(ends ? c.pipe_ends : c.pipe).empty()) && !(flags & CHEBTD_SINGLE_ORDER);
 }
 
 // Blocks of the first (last) pass of such a step.
 int step_blocks(const Ctx &c, bool ends, bool last)
 {
+    if (c.walk && !ends) return (int)(last ? 2 * reduce_blocks(c.n) : walk_head_blocks(c));
     if (c.tile.R) {
         const int D = last ? c.tile.depths.back() : c.tile.depths.front();
         return (int)(c.kind == HKind::Chain ? tile_blocks(c, c.tile.R, D) : ribbon_tile_blocks(c.L, D));
@@ -192,6 +195,10 @@ const char *pipe_names(const Ctx &c, int *npass, int *orders)
 hipError_t enqueue_step_pipe(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, double2 *ckpt, double2 *ends,
                              double *partials, double *knorm)
 {
+    if (c->walk && !ends) {
+        hipError_t e = enqueue_step_pairs(c, s, cur, nxt, ckpt, nullptr, partials, nullptr, nullptr);
+        return e == hipSuccess && knorm ? launch_norm(*c, s, nxt, knorm) : e;
+    }
     double2 *X = nullptr, *Y = cur;
     double2 *out[2][2] = {{static_cast<double2 *>(c->vA.p), static_cast<double2 *>(c->vC.p)},
                           {static_cast<double2 *>(c->vD.p), cur}};
@@ -293,7 +300,8 @@ hipError_t enqueue_step(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt, doubl
                         double *norm_out, double *energy_out, unsigned flags)
 {
     if (c->use_pairs && !(flags & CHEBTD_SINGLE_ORDER))
-        return enqueue_step_pairs(c, s, cur, nxt, ckpt, ends, norm_out, energy_out);
+        return enqueue_step_pairs(c, s, cur, nxt, ckpt, ends, static_cast<double *>(c->partials.p), norm_out,
+                                  energy_out);
     double2 *A = static_cast<double2 *>(c->vA.p);
     double *partials = static_cast<double *>(c->partials.p);
     hipError_t e = launch_head(*c, s, cur, A, nxt, weight(c, 0), weight(c, 1), ckpt, partials);
@@ -639,7 +647,7 @@ int chebtd_time_recursion_kernel(chebtd_ctx *ctx, int launches, unsigned flags, 
     Ctx *c = static_cast<Ctx *>(ctx);
     if (!c->has_plan) return fail(c, CHEBTD_E_STATE, "chebtd_time_recursion_kernel: no plan");
     if (launches < 1 || !ms_per_launch) return fail(c, CHEBTD_E_ARG, "need launches >= 1 and an output");
-    const bool pipe = use_pipe(*c, flags, false);
+    const bool pipe = use_pipe(*c, flags, false) && !c->walk;
     const bool pairs = !pipe && c->use_pairs && !(flags & CHEBTD_SINGLE_ORDER);
     // the multi-order kernel the step spends most of its passes in
     const int dp = pairs ? dominant_pass(*c) : 2;

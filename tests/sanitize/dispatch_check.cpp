@@ -94,12 +94,26 @@ static void room_given_back()
     CHECK(ensure(&c, b, size_t(1) << 50, "test") == CHEBTD_E_OOM && c.csr_buf.p == nullptr && b.p == nullptr);
 }
 
+// Steps of few orders on ribbons: one walk, not a pipelined pass of eight
+// orders; the benchmark's and the paper's steps stay where they are.
+static void few_orders()
+{
+    for (int M = 2; M <= 5; ++M) CHECK(walk_takes_step(128, 8192, M, false) && walk_takes_step(64, 1000, M, false));
+    CHECK(walk_takes_step(1024, 32768, 3, false) && walk_takes_step(1024, 32768, 6, false));
+    CHECK(!walk_takes_step(1024, 32768, 2, false) && !walk_takes_step(128, 8192, 6, false));
+    CHECK(walk_takes_step(40, 500, 3, true) && !walk_takes_step(10, 1000, 3, true));
+    for (int64_t W : {4, 16, 32, 48, 49, 128, 301, 1024, 30000})
+        for (int64_t L : {64, 512, 5003, 32768})
+            for (int M = 7; M <= 100; ++M) CHECK(!walk_takes_step(W, L, M, W <= 48));
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "chain") chain_residency();
     else if (what == "csr") csr_copies();
     else if (what == "room") room_given_back();
+    else if (what == "walk") few_orders();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;

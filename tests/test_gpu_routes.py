@@ -5,7 +5,7 @@ import pytest
 
 import oracle as O
 from test_gpu_deep import run
-from test_gpu_parity import _hermitian_csr, assert_state_close, chain_case, dev, gpu_context, host, say
+from test_gpu_parity import _hermitian_csr, assert_state_close, chain_case, dev, gpu_context, honey_case, host, say
 
 pytestmark = pytest.mark.gpu
 
@@ -154,3 +154,45 @@ def test_csr_uneven_rows_are_not_copied(torch, cheb, every, copied):
     _, name, _ = ctx.time_recursion_kernel(2)
     ctx.close()
     assert ("Copy" in name) == copied
+
+
+# steps of few orders on ribbons run as walks inside the run whose sums go over
+# several steps: every route with sums, checks, graphs and driven steps, more
+# steps than the sums in flight
+@pytest.mark.parametrize("w,l,edge,M,kernel", [(61, 300, "zigzag", 2, "k_pair"), (61, 300, "armchair", 3, "k_deep"),
+                                               (130, 131, "zigzag", 5, "k_deep"), (50, 70, "armchair", 6, "k_deep"),
+                                               (40, 500, "zigzag", 3, "k_deep"), (700, 9, "zigzag", 9, "k_deep"),
+                                               (700, 9, "armchair", 10, "k_deep"), (61, 300, "zigzag", 7, "k_pipe"),
+                                               (10, 300, "zigzag", 3, "k_ribbon_tile")])
+def test_steps_of_few_orders(torch, cheb, w, l, edge, M, kernel):
+    K, dt = 70, 0.05
+    case = honey_case(w, l, edge, state="dense")
+    say(f"[gpu] few orders {w}x{l} {edge} M={M}")
+    ctx, psi, nrm, en, plan = run(torch, cheb, case, dt, K, M=M)
+    assert ctx.time_recursion_kernel(2)[1].startswith(kernel)
+    ref, rn, re = O.propagate(case["H"], plan, case["psi0"], K, want_obs=True)
+    assert_state_close(psi, ref)
+    np.testing.assert_allclose(nrm, rn, rtol=1e-12)
+    np.testing.assert_allclose(en, re, rtol=1e-10, atol=1e-12)
+    # checked, without sums, replayed from a graph, driven by a constant on-site term
+    ctx.set_check_tol(1.0)
+    p = dev(torch, case["psi0"])
+    ctx.propagate(p, K)
+    np.testing.assert_array_equal(host(p), psi)
+    n2, e2 = torch.zeros(K, dtype=torch.float64, device="cuda"), torch.zeros(K, dtype=torch.float64, device="cuda")
+    for k in (K, 5):
+        p = dev(torch, case["psi0"])
+        n2.zero_()
+        ctx.propagate(p, k, n2, e2, cheb.GRAPH)
+        np.testing.assert_array_equal(host(n2)[:k], nrm[:k])
+        np.testing.assert_array_equal(host(e2)[:k], en[:k])
+    p = dev(torch, case["psi0"])
+    ctx.propagate_td(p, case["eps_dev"].repeat(K, 1), n2, e2)
+    np.testing.assert_array_equal(host(p), psi)
+    np.testing.assert_array_equal(host(n2), nrm)
+    # a state that is not finite still ends with the error
+    p = dev(torch, case["psi0"])
+    p[w * l // 2] = float("nan")
+    with pytest.raises(cheb.ChebError):
+        ctx.propagate(p, 3)
+    ctx.close()
