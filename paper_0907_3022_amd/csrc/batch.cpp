@@ -268,7 +268,8 @@ static int build_tables(Ctx *c, BatchState *b)
     std::vector<int32_t> dsys, dw0, dpsys, dpw0, dtsys, dttile;
     b->deep_launches.clear();
     b->deep_pair_off.assign(1, 0);
-    if (b->deep_ok) {
+    const bool deep_tables = b->deep_ok && !b->pipe_ok;
+    if (deep_tables) {
         const int D = b->deep_D, E = D + 1;
         int maxpass = 0, maxrest = 0;
         for (int s = 0; s < ns; ++s) {
@@ -324,7 +325,7 @@ static int build_tables(Ctx *c, BatchState *b)
          (rc = upload(c, b->tblk_sys, tsys.data(), tsys.size() * 4, "tail block table")) ||
          (rc = upload(c, b->tblk_tile, ttile.data(), ttile.size() * 4, "tail tile table"))))
         return rc;
-    if (b->deep_ok &&
+    if (deep_tables &&
         ((rc = upload(c, b->dblk_sys, dsys.data(), dsys.size() * 4, "deep block table")) ||
          (rc = upload(c, b->dblk_wave0, dw0.data(), dw0.size() * 4, "deep wavefront table")) ||
          (rc = upload(c, b->dpblk_sys, dpsys.data(), dpsys.size() * 4, "deep pair block table")) ||
@@ -605,8 +606,11 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         if (b->M[s] < 2) b->pairs_ok = false;  // the head of a pair level computes two orders
         sd.npass_pairs = b->M[s] >> 1;
     }
-    // deep schedule without the pipelined passes (a forced depth, systems past
-    // their offsets): passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
+    // deep schedule without the pipelined passes, which cost what eight orders
+    // cost: a forced depth, or no system past D orders (M = 5 everywhere: 8
+    // ribbons of 32 x 512 and more 53 us for four steps against 61 pipelined, 64
+    // of 100 x 2000 and more 942 against 1036; M = 6: 75 and 60, 1041 and 997).
+    // Passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
     // overrides) or D + 1 orders, so every system needs M >= D.  On these
     // HBM-bound passes a pass costs about the same whatever its depth
     // (measured on MI355X over the 256-ribbon workload: 1020, 1024 and 1062
@@ -640,6 +644,7 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         sd.kdeep = D * npass + next;
         sd.npass_deep = sd.ndeep + (M - sd.kdeep) / 2;
     }
+    const int Mmost = *std::max_element(b->M.begin(), b->M.end());
     b->order.resize(nsys);
     for (int s = 0; s < nsys; ++s) b->order[s] = s;
     std::stable_sort(b->order.begin(), b->order.end(), [&](int32_t x, int32_t y) { return b->M[x] > b->M[y]; });
@@ -648,7 +653,8 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         (rc = ensure(c, b->done, (size_t)nsys * sizeof(int32_t), "completion counters")) ||
         (rc = ensure(c, b->flag, sizeof(int32_t), "timeout flag")) ||
         (rc = upload(c, b->rw_dev, rw.data(), rw.size() * sizeof(double), "batch real weights")) ||
-        (b->deep_ok && !std::getenv("CHEBTD_BATCH_DEPTH") && (rc = build_pipe(c, b))) || (rc = build_tables(c, b))) {
+        (b->deep_ok && Mmost > b->deep_D && !std::getenv("CHEBTD_BATCH_DEPTH") && (rc = build_pipe(c, b))) ||
+        (rc = build_tables(c, b))) {
         batch_destroy(c);
         return rc;
     }

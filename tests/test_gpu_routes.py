@@ -196,3 +196,35 @@ def test_steps_of_few_orders(torch, cheb, w, l, edge, M, kernel):
     with pytest.raises(cheb.ChebError):
         ctx.propagate(p, 3)
     ctx.close()
+
+
+# a batch of five orders everywhere takes them in one walk, as one system does
+# with that depth; one system of six orders and all run pipelined
+@pytest.mark.parametrize("dt,orders", [(0.004, {5}), (0.00545, {5, 6})])
+def test_batch_of_few_orders(torch, cheb, monkeypatch, dt, orders):
+    import test_gpu_batch as B
+    specs = [(7, 300, 0.6, 2, "armchair"), (64, 513, 1.2, 9, "zigzag"), (33, 129, 0.9, 3, "zigzag"),
+             (5, 1025, 0.5, 5, "armchair")]
+    systems = B.make_systems(specs, torch)
+    ctx = cheb.Context()
+    ctx.batch_create(systems, dt)
+    assert {int(M) for M in ctx.batch_info()} == orders
+    ctx.batch_set_schedule(cheb.SCHED_DEEP, 1024, 256, 1)
+    say(f"[gpu] batch of few orders dt={dt}")
+    ctx.batch_propagate(3, cheb.GRAPH)
+    torch.cuda.synchronize()
+    monkeypatch.setenv("CHEBTD_DEPTH", "5")
+    for s in systems:
+        got = s["psi"].cpu().numpy()
+        ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
+        assert_state_close(got, ref)
+        if orders == {5}:
+            one = cheb.Context()
+            one.honeycomb(s["width"], s["length"], s["eps"], edge=s["edge"])
+            one.set_bounds(s["emin"], s["emax"])
+            one.plan(dt)
+            p = dev(torch, s["psi0"])
+            one.propagate(p, 3)
+            np.testing.assert_array_equal(host(p), got)
+            one.close()
+    ctx.close()
