@@ -208,6 +208,7 @@ void step_weights(double a, double b, double dt, int M, std::vector<double> &gam
 // and as real factors: gamma_k = phase (-i)^k r_k
 void step_weights(double a, double b, double dt, int M, std::vector<double> &gamma, std::vector<double> &r,
                   double2 *phase);
+int hol_sites_per_thread(const Ctx &c);  // of the Holstein walk
 // Whether a ribbon's step of M orders takes less time in single-wavefront passes
 // than pipelined or (tiled) in registers, and the blocks of such a step's head.
 bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled);

@@ -853,12 +853,19 @@ int64_t grid_blocks(const Ctx &c)
 // 7.7 / 10.8 / 15.1 at 437580 (9), 8.8 / 8.4 / 12.3 / 20.5 at 604656 (12), 14.1
 // / 12.7 / 13.2 / 19.1 at 923780 (10), 27.1 / 24.7 / 24.2 / 23.3 at 1.85M (10),
 // 55 / 55 / 61 / 43 at 3.9M (11); the L = 18 polaron 10.60 ms with all against
-// 10.82 for groups of nine.  hol_spt > 0 groups them
-static int hol_sites_per_thread(const Ctx &c)
+// 10.82 for groups of nine.  What a walk over all sites needs is configurations,
+// one per thread: us for two steps of order 16 with 1 / 2 / all sites, 244 / 240
+// / 277 at 82251 configurations and L = 4, 319 / 275 / 315 at 135751 (4), 452 / 398
+// / 453 at 134596 (6), 590 / 554 / 514 at 177100 (6), 462 / 403 / 384 at 211876
+// (4), 647 / 621 / 546 at 316251 (4); with three sites, where a group of two is
+// no smaller walk, 188 / 203 / 210 at 39711, 254 / 250 / 229 at 91881, 495 / 562 /
+// 358 at 302621.  hol_spt > 0 groups the sites
+int hol_sites_per_thread(const Ctx &c)
 {
     if (c.hol_spt > 0) return (int)std::min<int64_t>(c.hol_spt, c.hol_L);
-    const int want = c.n <= 500000 ? 1 : c.n <= 1400000 ? 2 : c.hol_L;
-    return std::min(want, c.hol_L);
+    const int64_t nconf = c.n / c.hol_L;
+    if (c.n > 1400000 || nconf >= 160000 || (c.hol_L <= 3 && nconf >= 70000)) return c.hol_L;
+    return std::min(c.n <= 500000 ? 1 : 2, c.hol_L);
 }
 
 static int64_t hol_walk_blocks(const Ctx &c)

@@ -107,6 +107,22 @@ static void few_orders()
             for (int M = 7; M <= 100; ++M) CHECK(!walk_takes_step(W, L, M, W <= 48));
 }
 
+// Sites per thread of the Holstein walk, by configurations: enough of them and
+// a thread walks all sites.
+static void holstein_sites()
+{
+    auto spt = [](int L, int64_t nconf) {
+        Ctx c;
+        c.kind = HKind::Holstein;
+        c.hol_L = L;
+        c.n = nconf * L;
+        return hol_sites_per_thread(c);
+    };
+    CHECK(spt(3, 302621) == 3 && spt(4, 211876) == 4 && spt(6, 177100) == 6 && spt(3, 91881) == 3);
+    CHECK(spt(3, 39711) == 1 && spt(4, 135751) == 2 && spt(10, 92378) == 2 && spt(10, 43758) == 1);
+    CHECK(spt(10, 184756) == 10 && spt(12, 1352078) == 12 && spt(1, 255) == 1 && spt(2, 32640) == 1);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -114,6 +130,7 @@ int main(int argc, char **argv)
     else if (what == "csr") csr_copies();
     else if (what == "room") room_given_back();
     else if (what == "walk") few_orders();
+    else if (what == "holstein") holstein_sites();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;
