@@ -214,7 +214,8 @@ int64_t walk_head_blocks(const Ctx &c)
 // norms, energies and the check, which costs a walked run a kernel more):
 //   more than 48 rows, M = 2 / 3 / 5 / 6: 0.39 / 0.43 / 0.67 / 0.81 (0.53 / 0.58
 //   / 0.78 / 0.89) at 64 x 1000, 0.61 / 0.53 / 0.71 / 1.03 (0.73 / 0.68 / 0.83 /
-//   1.10) at 128 x 8192, 0.79 with M = 6 at 100 x 20000, 1.37 / 0.62 / 0.94 / 1.11
+//   1.10) at 128 x 8192, 0.79 with M = 6 at 100 x 20000, 0.62 with M = 5 at 128 x
+//   40000, 1.37 / 0.62 / 0.94 / 1.11
 //   (1.51 / 0.75 / 0.98 / 1.18) at 500 x 8000, 1.19 / 0.65 / 0.67 / 0.80 (1.25 /
 //   0.74 / 0.75 / 0.86) at 1024 x 8192;
 //   33 to 48 rows, M = 2 / 3 / 4 / 5: 0.55 / 0.62 / 0.87 / 0.84 at 40 x 500, 0.80 /
@@ -231,7 +232,7 @@ bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled)
     if (!tiled) {
         if (M == 2) return n < 3 * Mi;
         if (M == 3) return true;
-        if (M == 4 || M == 5) return n < 3 * Mi || n >= 6 * Mi;
+        if (M == 4 || M == 5) return W <= 256 || n < 3 * Mi || n >= 6 * Mi;
         if (M == 6) return (n <= 96 * Ki && W <= Ki) || (W <= 128 && n >= 5 * Mi / 4) || n >= 6 * Mi;
         if (L > 40) return false;
         if (M == 9 || M == 10) return true;
