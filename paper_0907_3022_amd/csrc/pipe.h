@@ -71,9 +71,10 @@ int64_t pipe_blocks(const Ctx &c, const PipeShape &s);
 hipError_t launch_pipe(const Ctx &c, hipStream_t s, const PipeShape &sh, const PipeArgs &A, double *partials,
                        double *knorm);
 // Sums of `count` steps' head partials (stride doubles apart) into
-// norm_out/energy_out[first ..] (first read from and advanced in *counter if
-// given); check (host-visible, or null): check[0] = norm of step 0 when
-// first_step, check[2] = sum of the nk doubles at knorm when given.
+// norm_out/energy_out[first ..] (two steps, first read from and advanced in
+// *counter, if that is given: no check then); check (host-visible, or null):
+// check[0] = norm of step 0 when first_step, check[2] = sum of the nk doubles
+// at knorm when given.
 struct NeSteps {
     const double *partials;
     int64_t stride;
