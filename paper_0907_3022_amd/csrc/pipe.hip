@@ -160,13 +160,30 @@ int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus)
     int64_t best = 1;
     double bt = 1e300;
     const int64_t limit = std::min(most, std::max<int64_t>(1, 4 * slots / strips));
-    for (int64_t n = 1; n <= limit; ++n) {
-        const double t = pipe_rounds(strips * n, NW, num_cus) * pipe_iterations(DW, NW, (int32_t)W, (int32_t)n);
-        if (t < bt) {
-            bt = t;
-            best = n;
+    auto iterations = [&](int64_t n) { return pipe_iterations(DW, NW, (int32_t)W, (int32_t)n); };
+    // counts of as many rounds at a time: the fewest of them whose walks are as
+    // short as those of the most (a tall narrow ribbon has thousands of counts)
+    int64_t first = 1;
+    for (int64_t k = 0; first <= limit; ++k)
+        for (int64_t wgs : {k * slots + num_cus, (k + 1) * slots}) {
+            const int64_t end = std::min(limit, wgs / strips);
+            if (end < first) continue;
+            const int32_t it = iterations(end);
+            const double t = pipe_rounds(strips * end, NW, num_cus) * it;
+            if (t < bt) {
+                int64_t lo = first, hi = end;
+                while (lo < hi) {
+                    const int64_t mid = (lo + hi) / 2;
+                    if (iterations(mid) <= it)
+                        hi = mid;
+                    else
+                        lo = mid + 1;
+                }
+                bt = t;
+                best = lo;
+            }
+            first = end + 1;
         }
-    }
     return (int)best;
 }
 

@@ -1,10 +1,13 @@
 // Host-side check of the rules that choose a kernel or its launch shape.  Needs
 // no GPU; linked with the library's objects.  Exit status 0: every check passed.
+#include <algorithm>
+#include <chrono>
 #include <cstdio>
 #include <string>
 
 #include "chebtd.h"
 #include "internal.h"
+#include "pipe.h"
 
 using namespace chebtd;
 
@@ -123,6 +126,31 @@ static void holstein_sites()
     CHECK(spt(10, 184756) == 10 && spt(12, 1352078) == 12 && spt(1, 255) == 1 && spt(2, 32640) == 1);
 }
 
+// The row chunks of a pipelined pass: no count takes less time by the model, and
+// a plan of the tallest ribbon does not try every one.
+static void pipe_chunk_counts()
+{
+    const int shapes[][2] = {{2, 4}, {3, 4}, {4, 4}, {5, 4}, {3, 8}};
+    for (int64_t W : {1, 7, 30, 50, 64, 97, 128, 301, 777, 1024, 4099, 30000})
+        for (int64_t L : {2, 80, 200, 777, 1500, 5003, 8192, 32768})
+            for (const auto &sh : shapes) {
+                const int n = pipe_chunks(W, L, sh[0], sh[1], 256);
+                const double t = pipe_time(W, L, {{sh[0], sh[1], n}}, 256);
+                const int64_t most = (W - (sh[0] * sh[1] - 1)) / 8;
+                CHECK(n >= 1 && (n == 1 || n <= most));
+                const int64_t cols = pipe_strip_cols(sh[0] * sh[1]), strips = (L + cols - 1) / cols;
+                const int64_t places = sh[1] <= 4 ? 512 : 256;  // on 256 CUs; up to four rounds of them are tried
+                for (int64_t m = 1; m <= std::min(most, 4 * places / strips); ++m)
+                    CHECK(t <= pipe_time(W, L, {{sh[0], sh[1], (int)m}}, 256) * (1.0 + 1e-12));
+                if (failures > 20) return;
+            }
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 0; i < 1000; ++i) pipe_chunks(30000, 2, 5, 4, 256);
+    const double us = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() * 1e3;
+    std::printf("pipe_chunks at 30000 x 2: %.2f us\n", us);
+    CHECK(us < 25.0);  // 87 us when every count is tried, 1.3 now
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -131,6 +159,7 @@ int main(int argc, char **argv)
     else if (what == "room") room_given_back();
     else if (what == "walk") few_orders();
     else if (what == "holstein") holstein_sites();
+    else if (what == "chunks") pipe_chunk_counts();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;
