@@ -274,9 +274,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_batch_pipe(const SysDev *__restr
     A.r = rw + sd.rw_off + pb.k0;
     double s0 = 0.0, s1 = 0.0;
     if (sd.edge == CHEBTD_ZIGZAG)
-        pipe_block<CHEBTD_ZIGZAG, DW, NW>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
+        pipe_block<CHEBTD_ZIGZAG, DW, NW, false>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
     else
-        pipe_block<CHEBTD_ARMCHAIR, DW, NW>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
+        pipe_block<CHEBTD_ARMCHAIR, DW, NW, false>(op, A, pb.strip, pb.ys, pb.ye, slots, s0, s1);
 }
 
 // The last order M of a system its passes left one short: v_M = 2 H~ v_{M-1}

@@ -61,6 +61,19 @@ struct RowSet {
     double2 a[2], k[2], va[2], vk[2], p[2];
     double e[2], g[2];
 };
+__device__ __forceinline__ void arrived(const RowSet &n)
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        arrived(n.a[c]);
+        arrived(n.k[c]);
+        arrived(n.va[c]);
+        arrived(n.vk[c]);
+        arrived(n.p[c]);
+    }
+    arrived(n.e);
+    arrived(n.g);
+}
 
 // y += (-i)^n r x
 template <int n>
@@ -173,16 +186,7 @@ __device__ __forceinline__ void wave(const PipeOp &op, const RevPipeArgs &A, int
     } else {
         for (int32_t t = 0; t + 1 < sp.t0; ++t) row_barrier();
         fetch(set[0], 0);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            arrived(set[0].a[c]);
-            arrived(set[0].k[c]);
-            arrived(set[0].va[c]);
-            arrived(set[0].vk[c]);
-            arrived(set[0].p[c]);
-        }
-        arrived(set[0].e);
-        arrived(set[0].g);
+        arrived(set[0]);
         row_barrier();
     }
 
@@ -287,6 +291,7 @@ __device__ __forceinline__ void wave(const PipeOp &op, const RevPipeArgs &A, int
             put(at + 10 * 1024, make_double2(dd[sR][0], dd[sR][1]));
             put(at + 11 * 1024, make_double2(G[sR][0], G[sR][1]));
         }
+        if constexpr (!FIRST) arrived(set[(ph + 1) & 1]);
         row_barrier();
     };
     static_assert(kRevPipeDW == 2, "levels are written out");

@@ -79,8 +79,11 @@ __device__ __forceinline__ void row_barrier()
 // The loads of these values come before this point.  Without it the compiler
 // moves LDS reads whose first use lies behind a branch past a row_barrier() in
 // front of that branch, where the next wavefront's stores may overtake them.
-__device__ __forceinline__ void arrived(double2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-__device__ __forceinline__ void arrived(double (&v)[2]) { asm volatile("" : "+v"(v[0]), "+v"(v[1])); }
+// Every row read ahead passes here before the barrier, except in the loop of the
+// batched kernel, which has no registers left (1049 -> 1202 us for four steps of
+// 64 ribbons): there the built code's waits are what a test of it looks at.
+__device__ __forceinline__ void arrived(const double2 &v) { asm volatile("" ::"v"(v.x), "v"(v.y)); }
+__device__ __forceinline__ void arrived(const double (&v)[2]) { asm volatile("" ::"v"(v[0]), "v"(v[1])); }
 
 constexpr int kHead = 0, kHeadKeep = 1, kFirst = 2, kMid = 3, kLast = 4, kFinal = 5;
 
@@ -88,6 +91,16 @@ struct RowSet {
     double2 a[2], k[2], p[2];
     double e[2];
 };
+__device__ __forceinline__ void arrived(const RowSet &n)
+{
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        arrived(n.a[c]);
+        arrived(n.k[c]);
+        arrived(n.p[c]);
+    }
+    arrived(n.e);
+}
 
 // i^n (x + iy)
 template <int n>
@@ -112,7 +125,7 @@ __device__ __forceinline__ void add_order(int l, double r, double2 v, double2 &P
 // Wavefront w of the workgroup.  ROLE: kHead (a step's first pass; kHeadKeep
 // also copies psi) and kFirst read memory, kLast (acc and the last two orders)
 // and kFinal (acc alone) write it, kMid does neither.
-template <int EDGE, int DW, int NW, int ROLE>
+template <int EDGE, int DW, int NW, int ROLE, bool GUARD>
 __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w, int32_t strip, int32_t ys, int32_t ye,
                                      int32_t tend, PipeSlot (*slots)[2], double &s0, double &s1)
 {
@@ -211,13 +224,7 @@ __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w,
     } else {
         for (int32_t t = 0; t + 1 < sp.t0; ++t) row_barrier();
         fetch(set[0], rd[1]);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            arrived(set[0].a[c]);
-            arrived(set[0].k[c]);
-            arrived(set[0].p[c]);
-        }
-        arrived(set[0].e);
+        arrived(set[0]);
         row_barrier();
     }
 
@@ -313,6 +320,7 @@ __device__ __forceinline__ void wave(const PipeOp &op, const PipeArgs &A, int w,
             }
             q->d[lane] = make_double2(dd[sR][0], dd[sR][1]);
         }
+        if constexpr (!FIRST && GUARD) arrived(set[(ph + 1) % K]);
         row_barrier();
     };
     for (int32_t i = 0; i < sp.n; i += kUnroll, base += kUnroll) phases<0, kUnroll>(step);
@@ -336,7 +344,7 @@ __device__ __forceinline__ int pipe_wave()
 // The workgroup's share: strip `strip`, rows [ys, ye).  sums: <v0|v0> and
 // <v0|H~ v0> of a head pass (wavefront 0's lanes), sum |acc|^2 (the last
 // wavefront's).
-template <int EDGE, int DW, int NW>
+template <int EDGE, int DW, int NW, bool GUARD = true>
 __device__ __forceinline__ void pipe_block(const PipeOp &op, const PipeArgs &A, int32_t strip, int32_t ys, int32_t ye,
                                            PipeSlot (*slots)[2], double &s0, double &s1)
 {
@@ -350,18 +358,18 @@ __device__ __forceinline__ void pipe_block(const PipeOp &op, const PipeArgs &A, 
     }
     if (w == 0) {
         if (A.vkm1 == nullptr && A.ckpt == nullptr)
-            wave<EDGE, DW, NW, kHead>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
+            wave<EDGE, DW, NW, kHead, GUARD>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
         else if (A.vkm1 == nullptr)
-            wave<EDGE, DW, NW, kHeadKeep>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
+            wave<EDGE, DW, NW, kHeadKeep, GUARD>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
         else
-            wave<EDGE, DW, NW, kFirst>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
+            wave<EDGE, DW, NW, kFirst, GUARD>(op, A, 0, strip, ys, ye, tend, slots, s0, s1);
     } else if (w == NW - 1) {
         if (A.out2 == nullptr)
-            wave<EDGE, DW, NW, kFinal>(op, A, NW - 1, strip, ys, ye, tend, slots, s0, s1);
+            wave<EDGE, DW, NW, kFinal, GUARD>(op, A, NW - 1, strip, ys, ye, tend, slots, s0, s1);
         else
-            wave<EDGE, DW, NW, kLast>(op, A, NW - 1, strip, ys, ye, tend, slots, s0, s1);
+            wave<EDGE, DW, NW, kLast, GUARD>(op, A, NW - 1, strip, ys, ye, tend, slots, s0, s1);
     } else {
-        wave<EDGE, DW, NW, kMid>(op, A, w, strip, ys, ye, tend, slots, s0, s1);
+        wave<EDGE, DW, NW, kMid, GUARD>(op, A, w, strip, ys, ye, tend, slots, s0, s1);
     }
 }
 
