@@ -588,6 +588,7 @@ int chebtd_set_bounds(chebtd_ctx *ctx, double emin, double emax, double alpha)
 
 static int plan_common(Ctx *c, double dt, int M)
 {
+    c->has_plan = false;  // until this one is whole: an allocation below may fail
     step_weights(c->a, c->b, dt, M, c->gamma, c->rweight, &c->phase);
     int rc;
     // one upload: gamma, then the real factors padded for a last pass past M

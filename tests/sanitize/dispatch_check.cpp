@@ -14,6 +14,7 @@ using namespace chebtd;
 namespace chebtd {
 int ensure(Ctx *c, DevBuf &b, size_t bytes, const char *what);  // api.cpp
 }
+struct chebtd_ctx : public Ctx {};
 
 static int failures = 0;
 #define CHECK(cond)                                                                \
@@ -151,6 +152,23 @@ static void pipe_chunk_counts()
     CHECK(us < 25.0);  // 87 us when every count is tried, 1.3 now
 }
 
+// A plan whose allocations fail (there is no device here) leaves none behind:
+// buffers of the one before may be gone.
+static void failed_plan()
+{
+    chebtd_ctx c;
+    c.kind = HKind::Honeycomb;
+    c.W = 10;
+    c.L = 100;
+    c.n = 1000;
+    c.num_cus = 256;
+    c.a = 3.0;
+    c.has_bounds = c.has_plan = true;
+    CHECK(chebtd_plan_order(&c, 0.5, 12) != CHEBTD_OK && !c.has_plan);
+    double d = 0.0;
+    CHECK(chebtd_propagate(&c, &d, 1, nullptr, nullptr, 0) == CHEBTD_E_STATE);
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -160,6 +178,7 @@ int main(int argc, char **argv)
     else if (what == "walk") few_orders();
     else if (what == "holstein") holstein_sites();
     else if (what == "chunks") pipe_chunk_counts();
+    else if (what == "plan") failed_plan();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);
     return failures == 0 ? 0 : 1;
