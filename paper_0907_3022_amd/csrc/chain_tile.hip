@@ -28,19 +28,6 @@
 
 namespace chebtd {
 
-namespace {
-
-// i^n v, n uniform
-__device__ __forceinline__ double2 turn_by(int n, double2 v)
-{
-    const bool odd = n & 1;
-    const double x = odd ? v.y : v.x, y = odd ? v.x : v.y;
-    // 1: (-y, x), 2: (-x, -y), 3: (y, -x)
-    return make_double2((n & 3) == 1 || (n & 3) == 2 ? -x : x, (n & 3) >= 2 ? -y : y);
-}
-
-}  // namespace
-
 // INSIDE: every site of the wavefront lies on the chain
 template <int R, bool INSIDE>
 __device__ __forceinline__ void tile_wave(const TileOp &op, const TileArgs &A, int64_t base, double &s0, double &s1,

@@ -45,6 +45,15 @@ __device__ __forceinline__ double2 cfma(double2 g, double2 v, double2 a)
     return a;
 }
 
+// i^n v, n uniform
+__device__ __forceinline__ double2 turn_by(int n, double2 v)
+{
+    const bool odd = n & 1;
+    const double x = odd ? v.y : v.x, y = odd ? v.x : v.y;
+    // 1: (-y, x), 2: (-x, -y), 3: (y, -x)
+    return make_double2((n & 3) == 1 || (n & 3) == 2 ? -x : x, (n & 3) >= 2 ? -y : y);
+}
+
 __device__ __forceinline__ double wave_sum(double x)
 {
 #pragma unroll

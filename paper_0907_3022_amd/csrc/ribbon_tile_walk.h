@@ -37,14 +37,6 @@ namespace rtiledev {
 using namespace deepdev;
 using namespace pairdev;
 
-// i^n v, n uniform
-__device__ __forceinline__ double2 turn_by(int n, double2 v)
-{
-    const bool odd = n & 1;
-    const double x = odd ? v.y : v.x, y = odd ? v.x : v.y;
-    return make_double2((n & 3) == 1 || (n & 3) == 2 ? -x : x, (n & 3) >= 2 ? -y : y);
-}
-
 // edges: [2][NW + 2].  Wavefront w of NW = ceil(W / RW).
 template <int EDGE, int RW>
 __device__ __forceinline__ void wave(const PipeOp &op, const TileArgs &A, int w, int NW, int32_t strip,
