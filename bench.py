@@ -541,8 +541,9 @@ def bench_table2(torch, P):
         f = psi.cpu().numpy()
         finals.append(f)
         rho = np.abs(f) ** 2
-        runs.append(dict(dt=dt, M=M, steps=K, seconds=t, passes=ctx.plan_passes(), paper_seconds=paper_s,
-                         paper_M=paper_M, norm_deviation=abs(float(rho.sum()) - 1.0),
+        _, kname, orders = ctx.time_recursion_kernel(4)
+        runs.append(dict(dt=dt, M=M, steps=K, seconds=t, kernel=kname, orders_per_pass=orders,
+                         paper_seconds=paper_s, paper_M=paper_M, norm_deviation=abs(float(rho.sum()) - 1.0),
                          rms_distance_columns=float(np.sqrt((rho * (x - x0) ** 2).sum() / rho.sum())),
                          participation_fraction=float(rho.sum() ** 2 / (rho ** 2).sum() / rho.size)))
     ref = finals[0]

@@ -189,9 +189,12 @@ int chebtd_get_plan(const chebtd_ctx *ctx, double *gamma_host, double *a, double
 
 /* How M splits into single-wavefront passes (1D chains longer than the
  * whole-run chain kernels, honeycomb ribbons; M >= 2): the Chebyshev orders
- * each pass advances, in launch order.  Steps run this split where the
- * pipelined and tiled passes of 8 and more orders do not (lattices past their
- * 32-bit offsets, a forced CHEBTD_DEPTH); those are planned beside it.  The first pass is the step
+ * each pass advances, in launch order.  This split is planned for every such
+ * lattice, but most steps do not run it: pipelined passes of 8 to 24 orders or
+ * tiled ones of many take them (chebtd_time_recursion_kernel names the kernel
+ * that does and its orders).  It runs steps of a few orders on ribbons,
+ * lattices past the 32-bit offsets, a forced CHEBTD_DEPTH and CHEBTD_WALK=1.
+ * The first pass is the step
  * head (it also forms v_1 from psi); 2 runs the two-orders kernel, 3..6 the
  * deep kernel (that many orders of the recursion of Sect. 2.2 in one pass
  * over memory), 1 a single-order pass, only ever last.  The split is the
@@ -212,7 +215,10 @@ int chebtd_plan_passes(const chebtd_ctx *ctx, int *passes_out, int capacity, int
  * s (psi_s = state after s steps).  Unless CHEBTD_NO_CHECK is set the call
  * synchronises at the end and returns CHEBTD_E_DIVERGED if the final norm
  * is not finite or differs from the initial one by more than the check
- * tolerance (chebtd_set_check_tol, default 1e-6 relative).
+ * tolerance (chebtd_set_check_tol, default 1e-6 relative).  A value that is not
+ * finite reaches every site within M bonds in a step and may reach more: the
+ * pipelined and tiled passes take orders past M with weight 0 and bonds across
+ * the lattice's edge with factor 0, and 0 times it is NaN.
  * CHEBTD_KEEP_CHECKPOINTS stores psi_s for the adjoint (CHEBTD_ADJ_REVERSE:
  * also v_{M-1} and v_M of every step); it needs chebtd_reserve_adjoint with
  * K <= its max_steps.
@@ -325,7 +331,8 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
                                   /* CHEBTD_BATCH_DEPTH=D (4..6): passes of */
                                   /* D or D + 1 orders, the fewest that     */
                                   /* cover each M, then two-order and       */
-                                  /* one-order passes.  Needs M >= D (5)    */
+                                  /* one-order passes; those of D = 5 also  */
+                                  /* where no M is past 5.  Needs M >= D    */
                                   /* everywhere                             */
 
 /* Fix the schedule: mode, rows per tile (multiple of block, >= block),

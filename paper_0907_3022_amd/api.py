@@ -191,8 +191,9 @@ class Context:
         return dict(gamma=g, a=a.value, b=b.value, dt=dt.value, M=M.value)
 
     def plan_passes(self):
-        """Orders per pass of one step on the multi-order path ([] when the
-        plan runs one order per launch)."""
+        """How M splits into single-wavefront passes ([] when the plan runs one
+        order per launch).  Pipelined or tiled passes take most steps instead;
+        time_recursion_kernel() names the kernel that runs and its orders."""
         n = C.c_int()
         self._check(self._lib.chebtd_plan_passes(self.h, None, 0, C.byref(n)))
         out = np.zeros(max(n.value, 1), dtype=np.int32)

@@ -234,7 +234,9 @@ struct CsrRow {
     {
         return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
     }
-    // the same as apply2 from the copy of a real matrix: the sum in the same order
+    // the same as apply2 from the copy of a real matrix: the sum in the same order,
+    // the same bits of finite vectors (an infinite one keeps its sign: 0 times its
+    // other part is not added)
     __device__ static __forceinline__ double2 apply2_real(const OpCsrCopy &op, int64_t i, const double2 *v, double2 vi)
     {
         const int32_t p0 = op.rowptr32[i], len = op.rowptr32[i + 1] - p0;

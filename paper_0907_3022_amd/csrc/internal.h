@@ -168,7 +168,7 @@ struct Ctx {
     std::vector<int> passes;
     int deep_rows[kMaxDepth + 1] = {};  // rows per wavefront chunk of the deep kernel, by depth
     // pipelined passes of one step (pipe.h): ribbons of M >= 2, unless a depth
-    // is forced; empty: the passes above run
+    // is forced; empty, or `walk`: the passes above run
     std::vector<PipeShape> pipe;
     // the same for runs that keep each step's v_{M-1}, v_M: passes that add up
     // to M - pipe_rest orders, the rest in one deep or two-order pass

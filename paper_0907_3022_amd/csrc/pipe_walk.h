@@ -17,7 +17,9 @@
 // make the sublattice of every register a constant (no selects) and halve the
 // lane shifts, rows outside the lattice are cut off by a factor 0 on the
 // vertical bond instead of selects, columns outside by a zero hopping.  The
-// price is the halo, D columns per side and D - 1 rows above each chunk.
+// price is the halo, D columns per side and D - 1 rows above each chunk.  A value
+// that is not finite passes those factors as NaN: such a state spreads along the
+// lattice's edge and by the orders past M farther than the M bonds of a step.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -16,7 +16,8 @@
 // 32 -> 23, 40 x 32768 51 -> 45.  Past 48 rows the registers end: eight rows
 // per wavefront spill (64 x 1450: 32 -> 41 with the diagonal in LDS).
 //
-// A site's arithmetic is that of the pipelined passes, bit for bit.
+// A site's arithmetic is that of the pipelined passes, bit for bit; values that are
+// not finite spread along the edge as there.
 #pragma once
 
 #include <hip/hip_runtime.h>
