@@ -9,7 +9,8 @@
 // another pass follows) for all D orders: 40 B per site where one pass takes
 // the whole step.  No LDS, no barrier: wavefronts are independent.
 //
-// What bounds it: FP64 issue, 8 FP64 instructions per site and order and 8
+// What bounds it: a wavefront's issue and its dependent chain (half of its life
+// each, counted at 65536 sites), 8 FP64 instructions per site and order and 8
 // lane shifts per R sites; below about 10^5 sites the launch and the chain of
 // orders itself (0.10 us an order with four sites per lane).  Measured on
 // MI355X, us per step of 64 orders, passes of two and three orders before:

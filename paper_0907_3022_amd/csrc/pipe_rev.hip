@@ -10,10 +10,10 @@
 // hands on 96 B per row.  168 B per site and pass, as for the five levels of
 // the single-wavefront walk.
 //
-// What bounds it: the last-level cache or HBM (168 B per site for eight
-// levels), with FP64 issue (21 instructions and 8 lane shifts per site and
-// level, 4 on armchair edges) and LDS (2 x 96 B per column and two levels)
-// close behind: a strip's halo of 8 columns per side and the refill of every
+// What bounds it: at 512 x 16384 HBM (168 B per site for eight levels at a large
+// copy's rate); at 256 x 4096 a row of the slowest wavefront as in pipe_walk.h (21
+// instructions and 8 lane shifts per site and level, 4 on armchair edges, 0.76
+// wavefronts per SIMD, VALU busy 23%), with 4.65 TB/s counted beside it: a strip's halo of 8 columns per side and the refill of every
 // chunk weigh less than the second pass over memory that they save.  Measured
 // on MI355X, reverse run per step, single-wavefront passes of five levels ->
 // these: 256 x 4096 (64 orders) 503 -> 353 us (44 us a pass, 4.0 TB/s),

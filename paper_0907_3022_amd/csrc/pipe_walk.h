@@ -12,7 +12,11 @@
 // writes it: a whole step of D >= M orders reads psi and eps and writes the
 // next psi, 40 B per site.
 //
-// What bounds it: FP64 issue.  Per site and order 10 FP64 instructions (the
+// What bounds it: a row of the workgroup's slowest wavefront, two thirds of it
+// VALU issue, behind the barrier that ends every row (counted on MI355X: the
+// chip's VALU busy 54% of a pass at 1024 x 32768, 28% at 128 x 8192 with 188
+// workgroups on 256 CUs; a wavefront issues half of its life and waits a third
+// of it; 2.0 and 0.8 TB/s).  Per site and order 10 FP64 instructions (the
 // weights are real, see PipeArgs) and 4 lane shifts; two columns per lane
 // make the sublattice of every register a constant (no selects) and halve the
 // lane shifts, rows outside the lattice are cut off by a factor 0 on the

@@ -6,9 +6,10 @@
 // one column per side, so 128 - 4 ceil(D / 2) columns are the workgroup's own;
 // there is no halo in the rows.
 //
-// What bounds it: FP64 issue (10 FP64 instructions and 4 or 2 lane shifts per
-// site and order) and, for the few workgroups of a small ribbon, the launch
-// and the chain of orders.  Against the pipelined passes (pipe_walk.h) it has
+// What bounds it: the chain of orders, each a wavefront's issue (10 FP64
+// instructions and 4 or 2 lane shifts per site) and a barrier, at which it waits
+// as long (counted: issuing 36% of its life, waiting 38% at 10 x 1000), and for the
+// few workgroups of a small ribbon the launch.  Against the pipelined passes (pipe_walk.h) it has
 // no pipeline to fill and no rows to repeat, which is what a narrow ribbon
 // spends its time on there.  Measured on MI355X, us per step of 20 orders,
 // pipelined -> here: 6 x 200 17.6 -> 8.0, armchair 10 x 1000 19.9 -> 10.5 (69
