@@ -17,7 +17,7 @@ per site for a step in one pass: psi and the on-site term read, psi written;
 88 B per site for a single-order pass) over its mean launch time measured with
 HIP events on the library's stream, and its useful FP64 operations (20 per
 site and order) over the same time: with all orders of a step in one pass the
-kernel is bound by FP64 issue, not by HBM.
+kernel is bound by its wavefronts' issue and the barrier of every row, not by HBM.
 cpu_baseline: the serial CPU oracle on a few steps of the same workload.
 """
 from __future__ import annotations
@@ -757,7 +757,7 @@ def main():
         "config": {"workload": "zigzag_ribbon_128x8192", "sites": r["n"], "disorder_W": 0.5,
                    "dt": 1.0, "chebyshev_order": r["M"], "time_steps": args.steps,
                    "launch_mode": mode_name, "orders_per_pass": r["orders"], "complex128": True},
-        "roofline": {"bound": "hbm", "limiter": "fp64 issue",
+        "roofline": {"bound": "hbm", "limiter": "wavefront issue",
                      "fp64_tflops": tflops, "fp64_peak_tflops": FP64_PEAK_TFLOPS,
                      "fp64_frac": tflops / FP64_PEAK_TFLOPS,
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

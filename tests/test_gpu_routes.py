@@ -228,3 +228,33 @@ def test_batch_of_few_orders(torch, cheb, monkeypatch, dt, orders):
             np.testing.assert_array_equal(host(p), got)
             one.close()
     ctx.close()
+
+
+# checkpointing runs of few orders, walked, under each adjoint schedule
+@pytest.mark.parametrize("mode", ["ADJ_STEP", "ADJ_SQRTM", "ADJ_REVERSE"])
+@pytest.mark.parametrize("w,l,edge,M", [(61, 130, "zigzag", 2), (61, 130, "armchair", 3), (50, 70, "zigzag", 5),
+                                        (40, 90, "zigzag", 3), (700, 9, "zigzag", 9)])
+def test_gradients_of_few_orders(torch, cheb, w, l, edge, M, mode):
+    from test_gpu_adjoint import assert_grad_close, ribbon_inputs
+    K, dt = 3, 0.05
+    V, psi0, mask = ribbon_inputs(w, l, dense=True)
+    H = O.honeycomb(w, l, V, edge=edge)
+    lo, hi = H.gershgorin()
+    say(f"[gpu] gradient of few orders {w}x{l} {edge} M={M} {mode}")
+    ctx = cheb.Context()
+    Vd = dev(torch, V)
+    ctx.honeycomb(w, l, Vd, edge=edge)
+    ctx.set_bounds(lo, hi)
+    ctx.plan_order(dt, M)
+    assert ctx.time_recursion_kernel(1)[1].startswith(("k_deep", "k_pair"))
+    ctx.reserve_adjoint(K, getattr(cheb, mode))
+    psi = dev(torch, psi0)
+    ctx.propagate(psi, K, None, None, cheb.NO_CHECK | cheb.KEEP_CHECKPOINTS)
+    gbar = (2.0 * dev(torch, mask) * psi).contiguous()
+    dV = torch.zeros_like(Vd)
+    ctx.adjoint(gbar, dV)
+    torch.cuda.synchronize()
+    ctx.close()
+    _, gr, ur = O.adjoint(H, O.Plan(lo, hi, dt, M=M), psi0, K, mask)
+    assert_grad_close(host(dV), gr)
+    assert_state_close(host(gbar), ur)
