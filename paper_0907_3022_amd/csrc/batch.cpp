@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <fstream>
+#include <functional>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -119,8 +120,10 @@ static int upload(Ctx *c, DevBuf &d, const void *src, size_t bytes, const char *
 // Workgroup lists of the pipelined passes.  A pass over many systems has
 // workgroups enough with whole ribbons; otherwise the ribbons are cut into n
 // chunks each (8 rows or more), n with the least estimated time: the work
-// spread over the chip, but no less than the longest walk.  The longest walks
-// come first.
+// spread over the chip, but no less than the longest walks take.  Those come
+// first.  Four steps of order 20 with up to 16 chunks, counted in a smooth model,
+// and so: 3751 -> 348 us for one ribbon of 30000 x 16, 464 -> 200 for four of
+// 3000 x 16, 594 -> 386 for three of 4000 x 200.
 static int build_pipe(Ctx *c, BatchState *b)
 {
     const int ns = b->nsys;
@@ -159,22 +162,36 @@ static int build_pipe(Ctx *c, BatchState *b)
             };
             int best = 1;
             double bt = 1e300;
-            for (int n = 1; n <= 16; ++n) {
-                double sum = 0.0, longest = 0.0;
+            std::vector<std::pair<int32_t, int64_t>> walks;  // iterations, workgroups
+            for (int n = 1;; n += 1 + n / 16) {  // a few tall ribbons take hundreds
+                walks.clear();
+                double sum = 0.0;
                 bool more = n == 1;
                 for (int s : ids) {
                     const int32_t m = chunks(s, n);
                     more = more || m == n;
-                    const double it = pipe_iterations(x.DW, x.NW, b->sys[s].W, m);
-                    sum += it * strips(s) * m;
-                    longest = std::max(longest, it);
+                    walks.push_back({pipe_iterations(x.DW, x.NW, b->sys[s].W, m), (int64_t)strips(s) * m});
+                    sum += (double)walks.back().first * (double)walks.back().second;
                 }
                 if (!more) break;
-                const double t = std::max(sum / (double)slots, x.NW <= 4 ? 0.6 * longest : longest);
+                std::sort(walks.begin(), walks.end(), std::greater<std::pair<int32_t, int64_t>>());
+                // the k-th longest walk
+                auto walk = [&](int64_t k) {
+                    for (const auto &w : walks)
+                        if ((k -= w.second) < 0) return (double)w.first;
+                    return 0.0;
+                };
+                // the longest walk, 0.6 of its time alone on a CU that holds
+                // two, the one that joins it there, and the one that follows
+                // the first to end
+                const double first = walk(0);
+                const double t = std::max({sum / (double)slots,
+                                           x.NW <= 4 ? 0.6 * first + 0.4 * walk(c->num_cus) : first,
+                                           walk(slots) > 0.0 ? walk(slots - 1) + walk(slots) : 0.0});
                 if (t < 0.98 * bt) {
                     bt = t;
                     best = n;
-                } else if (t > 1.2 * bt) {
+                } else if (t > 1.2 * bt && sum > 2.0 * bt * (double)slots) {
                     break;  // more chunks only repeat more halo rows
                 }
             }

@@ -258,3 +258,23 @@ def test_gradients_of_few_orders(torch, cheb, w, l, edge, M, mode):
     _, gr, ur = O.adjoint(H, O.Plan(lo, hi, dt, M=M), psi0, K, mask)
     assert_grad_close(host(dV), gr)
     assert_state_close(host(gbar), ur)
+
+
+# a few tall ribbons in a batch are cut into hundreds of chunks, uneven ones
+# into different numbers
+@pytest.mark.parametrize("dt", [0.1, 1.0, 1.6])
+@pytest.mark.parametrize("specs", [[(900, 30, 0.6, 2, "armchair")],
+                                   [(1501, 9, 0.6, 2, "zigzag"), (333, 120, 1.2, 9, "armchair"), (40, 41, 0.9, 3, "zigzag")]])
+def test_batch_of_tall_ribbons(torch, cheb, specs, dt):
+    import test_gpu_batch as B
+    systems = B.make_systems(specs, torch)
+    ctx = cheb.Context()
+    ctx.batch_create(systems, dt)
+    ctx.batch_set_schedule(cheb.SCHED_DEEP, 1024, 256, 1)
+    say(f"[gpu] batch of tall ribbons dt={dt} M={ctx.batch_info()}")
+    ctx.batch_propagate(3, cheb.GRAPH)
+    torch.cuda.synchronize()
+    for s in systems:
+        ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
+        assert_state_close(s["psi"].cpu().numpy(), ref)
+    ctx.close()
