@@ -131,8 +131,23 @@ static int build_pipe(Ctx *c, BatchState *b)
     for (int s = 0; s < ns; ++s) total += b->nsites[s];
     std::vector<std::vector<PipeShape>> plan(ns);
     size_t maxpass = 0;
+    // Strips enough to fill the chip: the shapes by what a pass costs these
+    // ribbons (and 6 us), the same for all so that their passes share launches;
+    // with a sum for each system 300 of 5 x 100 took 268 us and not 193 (20 orders).
+    // By the number of sites alone flat ribbons took passes that are mostly
+    // filling and emptying. us for four steps before pipelined passes / by sites
+    // / now: one of 1 x 100000 with 33 orders 306 / 401 / 270, 64 of 2 x 2000 with
+    // 33 417 / 553 / 352, two of 4 x 200000 with 67 2229 / 2673 / 2212, 64 of
+    // 16 x 4000 with 33 2346 / 1644 / 1127. Fewer strips are cut into row chunks:
+    // there the number of sites decides.
+    int64_t wgs = 0;
+    double cost[kPipeShapes] = {6.0, 6.0, 6.0, 6.0, 6.0};
     for (int s = 0; s < ns; ++s) {
-        plan[s] = plan_pipe_shapes(total, b->M[s], false);
+        wgs += (b->sys[s].L + pipe_strip_cols(12) - 1) / pipe_strip_cols(12);
+        pipe_shape_costs(b->sys[s].W, b->sys[s].L, c->num_cus, cost);
+    }
+    for (int s = 0; s < ns; ++s) {
+        plan[s] = plan_pipe_shapes(total, b->M[s], false, wgs >= 2 * c->num_cus ? cost : nullptr);
         if (plan[s].empty()) return CHEBTD_OK;  // pipe_ok stays false
         maxpass = std::max(maxpass, plan[s].size());
     }
@@ -626,7 +641,8 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
     // deep schedule without the pipelined passes, which cost what eight orders
     // cost: a forced depth, or no system past D orders (M = 5 everywhere: 8
     // ribbons of 32 x 512 and more 53 us for four steps against 61 pipelined, 64
-    // of 100 x 2000 and more 942 against 1036; M = 6: 75 and 60, 1041 and 997).
+    // of 100 x 2000 and more 942 against 1036 by passes of 12 orders; M = 6: 75 and
+    // 60, 1041 and 805).
     // Passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
     // overrides) or D + 1 orders, so every system needs M >= D.  On these
     // HBM-bound passes a pass costs about the same whatever its depth

@@ -59,8 +59,12 @@ struct PipeArgs {
 std::vector<PipeShape> plan_pipe(const Ctx &c, int M, bool exact);
 // their estimated time, us
 double pipe_time(int64_t W, int64_t L, const std::vector<PipeShape> &passes, int num_cus);
-// the same without the chunks, for lattices of `sites` sites in all
-std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact);
+// adds what one ribbon of many costs a pass of each shape, us
+constexpr int kPipeShapes = 5;
+void pipe_shape_costs(int64_t W, int64_t L, int num_cus, double *cost);
+// the same without the chunks, for lattices of `sites` sites in all or by the cost
+// of a pass of each shape
+std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact, const double *cost = nullptr);
 // row chunks of a pass
 int pipe_chunks(int64_t W, int64_t L, int DW, int NW, int num_cus);
 // iterations of the longest walk when W rows are cut into n chunks

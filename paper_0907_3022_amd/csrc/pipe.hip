@@ -215,16 +215,33 @@ std::vector<PipeShape> plan_pipe(const Ctx &c, int M, bool exact)
     return out;
 }
 
-std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact)
+struct PipeCand {
+    int DW, NW;
+    double tiny, small, large;
+};
+static const PipeCand kPipeCands[kPipeShapes] = {{2, 4, 10.9, 26.0, 640.0}, {3, 4, 12.9, 32.0, 570.0},
+                                                 {4, 4, 15.4, 41.0, 645.0}, {5, 4, 18.8, 53.0, 700.0},
+                                                 {3, 8, 21.1, 62.0, 1090.0}};
+
+// Adds a ribbon's share of a pass over so many that every CU is full: the larger
+// of its workgroups' iterations, two of four wavefronts or one of eight sharing a
+// CU, and its bytes at 4.2 TB/s.
+void pipe_shape_costs(int64_t W, int64_t L, int num_cus, double *cost)
+{
+    for (int q = 0; q < kPipeShapes; ++q) {
+        const PipeCand &x = kPipeCands[q];
+        const double strips = (double)ceil_div(L, pipe_strip_cols(x.DW * x.NW));
+        const double it = pipe_iterations(x.DW, x.NW, (int32_t)W, 1);
+        const double us = x.NW <= 4 ? 0.5 * (0.14 + 0.12 * x.DW) : 0.55;
+        cost[q] += std::max(0.9 * strips * it * us / num_cus, 104.0 * (double)(W * L) / 4.2e6);
+    }
+}
+
+// cost: of each shape (or null: by the number of sites)
+std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact, const double *cost)
 {
     std::vector<PipeShape> out;
     if (M < 2 || std::getenv("CHEBTD_DEPTH")) return out;
-    struct Cand {
-        int DW, NW;
-        double tiny, small, large;
-    };
-    static const Cand cands[] = {{2, 4, 10.9, 26.0, 640.0}, {3, 4, 12.9, 32.0, 570.0}, {4, 4, 15.4, 41.0, 645.0},
-                                 {5, 4, 18.8, 53.0, 700.0}, {3, 8, 21.1, 62.0, 1090.0}};
     int fdw = 0, fnw = 0;
     if (const char *env = std::getenv("CHEBTD_PIPE"))
         if (std::sscanf(env, "%d,%d", &fdw, &fnw) != 2) return out;
@@ -232,11 +249,14 @@ std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact)
     std::vector<int> from((size_t)M + 1, -1);
     best[0] = 0.0;
     for (int m = 1; m <= M; ++m)
-        for (int q = 0; q < (int)(sizeof cands / sizeof cands[0]); ++q) {
-            const Cand &x = cands[q];
+        for (int q = 0; q < kPipeShapes; ++q) {
+            const PipeCand &x = kPipeCands[q];
             if ((fdw && (x.DW != fdw || x.NW != fnw)) || (exact && x.DW * x.NW > m)) continue;
             const double t = best[(size_t)std::max(0, m - x.DW * x.NW)] +
-                             (sites < (int64_t(1) << 17) ? x.tiny : sites < (int64_t(1) << 22) ? x.small : x.large);
+                             (cost                           ? cost[q]
+                              : sites < (int64_t(1) << 17)   ? x.tiny
+                              : sites < (int64_t(1) << 22)   ? x.small
+                                                             : x.large);
             if (t < best[(size_t)m]) {
                 best[(size_t)m] = t;
                 from[(size_t)m] = q;
@@ -244,7 +264,7 @@ std::vector<PipeShape> plan_pipe_shapes(int64_t sites, int M, bool exact)
         }
     for (int m = M; m > 0;) {
         if (from[(size_t)m] < 0) return {};
-        const Cand &x = cands[from[(size_t)m]];
+        const PipeCand &x = kPipeCands[from[(size_t)m]];
         out.push_back({x.DW, x.NW, 1});
         m -= x.DW * x.NW;
     }

@@ -152,6 +152,37 @@ static void pipe_chunk_counts()
     CHECK(us < 25.0);  // 87 us when every count is tried, 1.3 now
 }
 
+// The passes of a batch whose strips fill the chip: they hold every order, cost no
+// more than those by the number of sites, and those of ribbons of one row, mostly
+// filling and emptying where a pass holds many orders, hold twelve at most.
+static void shapes_by_cost()
+{
+    const int shapes[][2] = {{2, 4}, {3, 4}, {4, 4}, {5, 4}, {3, 8}};
+    for (int64_t W : {1, 2, 5, 16, 40, 100, 3000})
+        for (int64_t L : {100000, 400000}) {
+            double cost[kPipeShapes] = {};
+            pipe_shape_costs(W, L, 256, cost);
+            const auto sum = [&](const std::vector<PipeShape> &v, int &orders) {
+                double t = 0.0;
+                orders = 0;
+                for (const PipeShape &p : v) {
+                    orders += p.DW * p.NW;
+                    for (int q = 0; q < kPipeShapes; ++q)
+                        if (shapes[q][0] == p.DW && shapes[q][1] == p.NW) t += cost[q];
+                }
+                return t;
+            };
+            for (int M = 2; M < 140; ++M) {
+                int here = 0, there = 0;
+                const auto plan = plan_pipe_shapes(W * L, M, false, cost);
+                const double t = sum(plan, here), by_sites = sum(plan_pipe_shapes(W * L, M, false), there);
+                CHECK(here >= M && there >= M && t <= by_sites * (1.0 + 1e-12));
+                for (const PipeShape &p : plan) CHECK(W > 1 || p.DW * p.NW <= 12);
+                if (failures > 20) return;
+            }
+        }
+}
+
 // A plan whose allocations fail (there is no device here) leaves none behind:
 // buffers of the one before may be gone.
 static void failed_plan()
@@ -178,6 +209,7 @@ int main(int argc, char **argv)
     else if (what == "walk") few_orders();
     else if (what == "holstein") holstein_sites();
     else if (what == "chunks") pipe_chunk_counts();
+    else if (what == "shapes") shapes_by_cost();
     else if (what == "plan") failed_plan();
     else CHECK(!"known check");
     std::printf("dispatch_check %s: %d failures\n", what.c_str(), failures);

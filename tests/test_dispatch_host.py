@@ -26,7 +26,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["chain", "csr", "room", "walk", "holstein", "chunks", "plan"])
+@pytest.mark.parametrize("what", ["chain", "csr", "room", "walk", "holstein", "chunks", "shapes", "plan"])
 def test_dispatch_rules(driver, what):
     r = subprocess.run([driver, what], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
     assert r.returncode == 0 and ": 0 failures" in r.stdout, r.stdout

@@ -278,3 +278,22 @@ def test_batch_of_tall_ribbons(torch, cheb, specs, dt):
         ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
         assert_state_close(s["psi"].cpu().numpy(), ref)
     ctx.close()
+
+
+# batches whose strips fill the chip, of flat ribbons, alike and not
+@pytest.mark.parametrize("dt", [0.4, 1.6])
+@pytest.mark.parametrize("specs", [[(1, 120001, 0.6, 2, "armchair")],
+                                   [(2, 60000, 0.6, 2, "zigzag"), (1, 70003, 1.2, 9, "armchair"), (31, 900, 0.9, 3, "zigzag")]])
+def test_batch_of_flat_ribbons(torch, cheb, specs, dt):
+    import test_gpu_batch as B
+    systems = B.make_systems(specs, torch)
+    ctx = cheb.Context()
+    ctx.batch_create(systems, dt)
+    ctx.batch_set_schedule(cheb.SCHED_DEEP, 1024, 256, 1)
+    say(f"[gpu] batch of flat ribbons dt={dt} M={ctx.batch_info()}")
+    ctx.batch_propagate(3, cheb.GRAPH)
+    torch.cuda.synchronize()
+    for s in systems:
+        ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
+        assert_state_close(s["psi"].cpu().numpy(), ref)
+    ctx.close()
