@@ -403,6 +403,21 @@ void batch_deep_split(int M, int D, int *npass, int *next)
     }
 }
 
+// Systems whose steps single-wavefront passes of D and D + 1 orders run in less
+// time than pipelined passes, which cost what eight orders cost: those of D orders
+// (M = 5 everywhere: 8 ribbons of 32 x 512 and more 53 us for four steps against 61
+// pipelined, 64 of 100 x 2000 and more 942 against 1036 by passes of 12 orders;
+// M = 6: 75 and 60, 1041 and 805), and tall ribbons of few columns where one alone
+// walks and no pass of one or two orders is left (M = 10: one of 30000 x 16 176
+// against 250, four of 3000 x 16 132 against 139; six of 700 x 9 94 and 87).
+bool batch_walk_takes(int64_t W, int64_t L, int M, int D)
+{
+    if (M <= D) return true;
+    int npass = 0, next = 0;
+    batch_deep_split(M, D, &npass, &next);
+    return W >= 2048 && L <= 40 && D * npass + next == M && walk_takes_step(W, L, M, false);
+}
+
 static hipError_t enqueue_step(Ctx *c, BatchState *b, hipStream_t s, int par)
 {
     const SysDev *sys = static_cast<const SysDev *>(b->sys_dev.p);
@@ -638,13 +653,10 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         if (b->M[s] < 2) b->pairs_ok = false;  // the head of a pair level computes two orders
         sd.npass_pairs = b->M[s] >> 1;
     }
-    // deep schedule without the pipelined passes, which cost what eight orders
-    // cost: a forced depth, or no system past D orders (M = 5 everywhere: 8
-    // ribbons of 32 x 512 and more 53 us for four steps against 61 pipelined, 64
-    // of 100 x 2000 and more 942 against 1036 by passes of 12 orders; M = 6: 75 and
-    // 60, 1041 and 805).
-    // Passes of D = deep_D (CHEBTD_BATCH_DEPTH, 4 .. 6,
-    // overrides) or D + 1 orders, so every system needs M >= D.  On these
+    // deep schedule, without the pipelined passes at a forced depth or where
+    // batch_walk_takes says so for every system.  Passes of D = deep_D
+    // (CHEBTD_BATCH_DEPTH, 4 .. 6, overrides) or D + 1 orders, so every system
+    // needs M >= D.  On these
     // HBM-bound passes a pass costs about the same whatever its depth
     // (measured on MI355X over the 256-ribbon workload: 1020, 1024 and 1062
     // us for four, five and six orders; a two-order pass 1042 us over the
@@ -677,7 +689,9 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         sd.kdeep = D * npass + next;
         sd.npass_deep = sd.ndeep + (M - sd.kdeep) / 2;
     }
-    const int Mmost = *std::max_element(b->M.begin(), b->M.end());
+    bool walked = true;
+    for (int s = 0; s < nsys; ++s)
+        walked = walked && batch_walk_takes(b->sys[s].W, b->sys[s].L, b->M[s], b->deep_D);
     b->order.resize(nsys);
     for (int s = 0; s < nsys; ++s) b->order[s] = s;
     std::stable_sort(b->order.begin(), b->order.end(), [&](int32_t x, int32_t y) { return b->M[x] > b->M[y]; });
@@ -686,7 +700,7 @@ int chebtd_batch_create(chebtd_ctx *ctx, int nsys, const chebtd_sys_desc *descs,
         (rc = ensure(c, b->done, (size_t)nsys * sizeof(int32_t), "completion counters")) ||
         (rc = ensure(c, b->flag, sizeof(int32_t), "timeout flag")) ||
         (rc = upload(c, b->rw_dev, rw.data(), rw.size() * sizeof(double), "batch real weights")) ||
-        (b->deep_ok && Mmost > b->deep_D && !std::getenv("CHEBTD_BATCH_DEPTH") && (rc = build_pipe(c, b))) ||
+        (b->deep_ok && !walked && !std::getenv("CHEBTD_BATCH_DEPTH") && (rc = build_pipe(c, b))) ||
         (rc = build_tables(c, b))) {
         batch_destroy(c);
         return rc;

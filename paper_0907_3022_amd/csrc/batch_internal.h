@@ -81,6 +81,7 @@ hipError_t launch_batch_tail(hipStream_t s, const SysDev *sys, const double2 *ga
 hipError_t launch_batch_clear_flag(hipStream_t s, int32_t *flag);
 // the deep schedule's passes for M orders at depth D (batch.cpp)
 void batch_deep_split(int M, int D, int *npass, int *next);
+bool batch_walk_takes(int64_t W, int64_t L, int M, int D);
 // pipelined pass `pass` (DW orders in each of NW wavefronts) of the listed
 // workgroups; rw: the systems' real weights
 hipError_t launch_batch_pipe(hipStream_t s, int DW, int NW, const SysDev *sys, const double *rw, const PipeBlk *blks,

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <string>
 
+#include "batch_internal.h"
 #include "chebtd.h"
 #include "internal.h"
 #include "pipe.h"
@@ -111,6 +112,19 @@ static void few_orders()
             for (int M = 7; M <= 100; ++M) CHECK(!walk_takes_step(W, L, M, W <= 48));
 }
 
+// and in batches: the systems of the walk's depth, tall ribbons of few columns
+static void few_orders_batched()
+{
+    CHECK(batch_walk_takes(100, 2000, 5, 5) && !batch_walk_takes(100, 2000, 6, 5));
+    CHECK(batch_walk_takes(30000, 16, 10, 5) && batch_walk_takes(3000, 16, 10, 5));
+    CHECK(!batch_walk_takes(2000, 16, 10, 5) && !batch_walk_takes(3000, 41, 10, 5));
+    for (int M = 6; M <= 100; ++M) {
+        int np = 0, ne = 0;
+        batch_deep_split(M, 5, &np, &ne);
+        CHECK(!batch_walk_takes(128, 8192, M, 5) && (!batch_walk_takes(30000, 16, M, 5) || 5 * np + ne == M));
+    }
+}
+
 // Sites per thread of the Holstein walk, by configurations: enough of them and
 // a thread walks all sites.
 static void holstein_sites()
@@ -206,7 +220,7 @@ int main(int argc, char **argv)
     if (what == "chain") chain_residency();
     else if (what == "csr") csr_copies();
     else if (what == "room") room_given_back();
-    else if (what == "walk") few_orders();
+    else if (what == "walk") few_orders(), few_orders_batched();
     else if (what == "holstein") holstein_sites();
     else if (what == "chunks") pipe_chunk_counts();
     else if (what == "shapes") shapes_by_cost();

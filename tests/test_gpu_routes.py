@@ -297,3 +297,24 @@ def test_batch_of_flat_ribbons(torch, cheb, specs, dt):
         ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
         assert_state_close(s["psi"].cpu().numpy(), ref)
     ctx.close()
+
+
+# tall ribbons of few columns in a batch run two single-wavefront passes a step
+# of ten orders, where all are such
+@pytest.mark.parametrize("specs", [[(2200, 16, 0.6, 2, "zigzag"), (3001, 9, 0.6, 9, "armchair")],
+                                   [(2200, 16, 0.6, 2, "zigzag"), (3001, 41, 0.6, 9, "armchair")]])
+def test_batch_of_tall_narrow_ribbons(torch, cheb, specs):
+    import test_gpu_batch as B
+    systems = B.make_systems(specs, torch)
+    dt = next(float(t) for t in np.arange(0.01, 0.2, 0.001)
+              if all(O.Plan(s["emin"], s["emax"], t).M == 10 for s in systems))
+    ctx = cheb.Context()
+    ctx.batch_create(systems, dt)
+    ctx.batch_set_schedule(cheb.SCHED_DEEP, 1024, 256, 1)
+    say(f"[gpu] batch of tall narrow ribbons dt={dt} M={ctx.batch_info()}")
+    ctx.batch_propagate(3, cheb.GRAPH)
+    torch.cuda.synchronize()
+    for s in systems:
+        ref = O.propagate(s["H"], O.Plan(s["emin"], s["emax"], dt), s["psi0"], 3)
+        assert_state_close(s["psi"].cpu().numpy(), ref)
+    ctx.close()
