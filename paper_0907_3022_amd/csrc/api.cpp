@@ -251,6 +251,19 @@ bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled)
     return false;
 }
 
+// Chain steps of 2 to 4 orders that keep the step-end pairs: a tiled pass stores
+// four vectors, each lane its own few sites and the lines at a wavefront's ends
+// shared with the next, and falls behind where they leave the last-level cache.
+// Measured on MI355X over three kept steps, walked / tiled us: M = 2 at 600000 / 800000 / 1.5M
+// / 4M sites 76 / 80, 88 / 133, 116 / 263, 319 / 514; M = 3 at 1M / 1.5M / 4M 146 /
+// 114, 183 / 255, 463 / 515; M = 4 at 1M / 1.5M / 4M 145 / 115, 187 / 208, 584 / 464;
+// M = 5 and up tiled.
+bool walk_takes_kept_chain_step(int64_t n, int M)
+{
+    if (M == 2) return n >= 600000;
+    return (M == 3 && n >= 1300000) || (M == 4 && n >= 1300000 && n <= 3000000);
+}
+
 void invalidate_h(Ctx *c, bool csr = false)
 {
     if (!csr) release(c->csr_buf);
@@ -626,6 +639,8 @@ static int plan_common(Ctx *c, double dt, int M)
             pipe_time(c->W, c->L, c->pipe, c->num_cus) < us)
             c->tile.R = 0;
     }
+    c->walk_ends = c->kind == HKind::Chain && c->use_pairs && !std::getenv("CHEBTD_TILE") &&
+                   walk_takes_kept_chain_step(c->n, M);
     c->walk = false;
     if (c->kind == HKind::Honeycomb && c->use_pairs && (c->tile.R || !c->pipe.empty())) {
         bool forced = false;  // a shape to run in any case

@@ -175,6 +175,7 @@ struct Ctx {
     std::vector<PipeShape> pipe_ends;
     int pipe_rest = 0;
     TilePlan tile;           // tiled passes of chains and narrow ribbons
+    bool walk_ends = false;  // a chain's steps with step-end pairs run `passes` (walk_takes_kept_chain_step)
     bool walk = false;       // steps without step-end pairs run `passes` all the same (walk_takes_step)
     int pipe_ring = 0;       // steps whose head partials are in flight
     int64_t pipe_part = 0;   // doubles per step of them
@@ -212,6 +213,7 @@ int hol_sites_per_thread(const Ctx &c);  // of the Holstein walk
 // Whether a ribbon's step of M orders takes less time in single-wavefront passes
 // than pipelined or (tiled) in registers, and the blocks of such a step's head.
 bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled);
+bool walk_takes_kept_chain_step(int64_t n, int M);  // the same on chains, with step-end pairs
 int64_t walk_head_blocks(const Ctx &c);
 void shift_scale(double emin, double emax, double alpha, double *a, double *b);
 

@@ -145,6 +145,7 @@ hipError_t enqueue_step_pairs(Ctx *c, hipStream_t s, double2 *cur, double2 *nxt,
 // a padded last pipelined pass does not form.
 bool use_pipe(const Ctx &c, unsigned flags, bool ends)
 {
+    if (ends && c.walk_ends) return false;
     return (c.tile.R || (c.walk && !ends) || !(ends ? c.pipe_ends : c.pipe).empty()) && !(flags & CHEBTD_SINGLE_ORDER);
 }
 

@@ -112,6 +112,15 @@ static void few_orders()
             for (int M = 7; M <= 100; ++M) CHECK(!walk_takes_step(W, L, M, W <= 48));
 }
 
+// and chains that keep the step-end pairs: few orders of long chains
+static void few_orders_kept()
+{
+    CHECK(walk_takes_kept_chain_step(1500000, 2) && walk_takes_kept_chain_step(1500000, 3));
+    CHECK(!walk_takes_kept_chain_step(65536, 2) && !walk_takes_kept_chain_step(4000000, 4));
+    for (int64_t n : {4097, 65536, 1048576, 4000000, 6000000})
+        for (int M = 5; M <= 200; ++M) CHECK(!walk_takes_kept_chain_step(n, M));
+}
+
 // and in batches: the systems of the walk's depth, tall ribbons of few columns
 static void few_orders_batched()
 {
@@ -220,7 +229,7 @@ int main(int argc, char **argv)
     if (what == "chain") chain_residency();
     else if (what == "csr") csr_copies();
     else if (what == "room") room_given_back();
-    else if (what == "walk") few_orders(), few_orders_batched();
+    else if (what == "walk") few_orders(), few_orders_kept(), few_orders_batched();
     else if (what == "holstein") holstein_sites();
     else if (what == "chunks") pipe_chunk_counts();
     else if (what == "shapes") shapes_by_cost();

@@ -260,6 +260,34 @@ def test_gradients_of_few_orders(torch, cheb, w, l, edge, M, mode):
     assert_state_close(host(gbar), ur)
 
 
+# chains whose kept steps of few orders are walked, and one below
+@pytest.mark.parametrize("n,M", [(600001, 2), (599999, 2), (1300007, 3), (1300007, 4)])
+def test_gradients_of_few_orders_on_long_chains(torch, cheb, n, M):
+    import workloads as W
+    from test_gpu_adjoint import assert_grad_close
+    K, dt, dx = 2, 0.05, 0.8
+    V, psi0, mask = W.random_weights(n, 400 + M), W.random_state(n, 500 + M), W.random_weights(n, 600 + M)
+    H = O.chain1d(V, dx)
+    lo, hi = H.gershgorin()
+    say(f"[gpu] gradient of few orders on a chain of {n} M={M}")
+    ctx = cheb.Context()
+    Vd = dev(torch, V)
+    ctx.chain1d(Vd, dx)
+    ctx.set_bounds(lo, hi)
+    ctx.plan_order(dt, M)
+    ctx.reserve_adjoint(K, cheb.ADJ_REVERSE)
+    psi = dev(torch, psi0)
+    ctx.propagate(psi, K, None, None, cheb.NO_CHECK | cheb.KEEP_CHECKPOINTS)
+    gbar = (2.0 * dev(torch, mask) * psi).contiguous()
+    dV = torch.zeros_like(Vd)
+    ctx.adjoint(gbar, dV)
+    torch.cuda.synchronize()
+    ctx.close()
+    _, gr, ur = O.adjoint(H, O.Plan(lo, hi, dt, M=M), psi0, K, mask)
+    assert_grad_close(host(dV), gr)
+    assert_state_close(host(gbar), ur)
+
+
 # a few tall ribbons in a batch are cut into hundreds of chunks, uneven ones
 # into different numbers
 @pytest.mark.parametrize("dt", [0.1, 1.0, 1.6])
