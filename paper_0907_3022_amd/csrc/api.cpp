@@ -217,12 +217,15 @@ int64_t walk_head_blocks(const Ctx &c)
 //   1.10) at 128 x 8192, 0.79 with M = 6 at 100 x 20000, 0.62 with M = 5 at 128 x
 //   40000, 1.37 / 0.62 / 0.94 / 1.11
 //   (1.51 / 0.75 / 0.98 / 1.18) at 500 x 8000, 1.19 / 0.65 / 0.67 / 0.80 (1.25 /
-//   0.74 / 0.75 / 0.86) at 1024 x 8192;
+//   0.74 / 0.75 / 0.86) at 1024 x 8192; M = 4 / 5 / 6 with 64 to 8192 rows 0.82 to
+//   1.15 / 0.77 to 1.15 / 0.96 to 1.27 at 3.2 x 2^20 sites, 0.54 to 1.06 / 0.56 to 1.05 /
+//   0.77 to 1.23 at 2^22, 0.58 to 0.71 / 0.64 to 0.74 / 0.72 to 1.03 at 5 x 2^20;
 //   33 to 48 rows, M = 2 / 3 / 4 / 5: 0.55 / 0.62 / 0.87 / 0.84 at 40 x 500, 0.80 /
 //   0.77 / 1.06 / 1.00 at 40 x 10000, 1.28 / 0.72 / 0.99 / 0.86 at 40 x 40000, 1.79 /
 //   0.64 / 0.86 / 0.83 at 40 x 120000; M = 6 above 0.94;
 //   17 to 32 rows, M = 2 / 3: 0.74 / 0.87 at 32 x 500, 1.08 / 1.08 at 32 x 8000,
-//   1.70 / 0.75 at 32 x 100000; up to 16 rows, and M >= 4, above 1;
+//   1.70 / 0.75 at 32 x 100000; up to 16 rows, and M >= 4, above 1, but for one row
+//   and M = 2 (1.02 / 0.85 / 0.75 / 0.99 / 0.81 at 0.5 / 1 / 2 / 4 / 8 x 2^20 sites);
 //   a third of a strip's columns or fewer (one strip, mostly idle lanes), two
 //   passes of five orders (M = 9, 10): 0.88 at 3000 x 16, 0.68 at 30000 x 16, where
 //   M = 11 / 15 / 25 take 0.89 / 0.87 / 0.78; 1.12 at 3000 x 60.
@@ -231,9 +234,8 @@ bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled)
     const int64_t n = W * L, Ki = 1 << 10, Mi = 1 << 20;
     if (!tiled) {
         if (M == 2) return n < 3 * Mi;
-        if (M == 3) return true;
-        if (M == 4 || M == 5) return W <= 256 || n < 3 * Mi || n >= 6 * Mi;
-        if (M == 6) return (n <= 96 * Ki && W <= Ki) || (W <= 128 && n >= 5 * Mi / 4) || n >= 6 * Mi;
+        if (M <= 5) return true;
+        if (M == 6) return (n <= 96 * Ki && W <= Ki) || (W <= 128 && n >= 5 * Mi / 4) || n >= 9 * Mi / 2;
         if (L > 40) return false;
         if (M == 9 || M == 10) return true;
         return W >= 8 * Ki && L >= 8 && (M == 11 || M == 15 || M == 25);
@@ -248,7 +250,7 @@ bool walk_takes_step(int64_t W, int64_t L, int M, bool tiled)
         if (M == 2) return n <= 64 * Ki;
         return M == 3 && ((W > 24 && n <= 64 * Ki) || n >= 7 * Mi / 4);
     }
-    return false;
+    return W == 1 && M == 2 && n >= 3 * Mi / 4;
 }
 
 // Chain steps of 2 to 4 orders that keep the step-end pairs: a tiled pass stores

@@ -105,6 +105,8 @@ static void few_orders()
 {
     for (int M = 2; M <= 5; ++M) CHECK(walk_takes_step(128, 8192, M, false) && walk_takes_step(64, 1000, M, false));
     CHECK(walk_takes_step(1024, 32768, 3, false) && walk_takes_step(1024, 32768, 6, false));
+    CHECK(walk_takes_step(1500, 3495, 4, false) && walk_takes_step(777, 6748, 6, false));
+    CHECK(walk_takes_step(1, 2000000, 2, true) && !walk_takes_step(1, 300000, 2, true));
     CHECK(!walk_takes_step(1024, 32768, 2, false) && !walk_takes_step(128, 8192, 6, false));
     CHECK(walk_takes_step(40, 500, 3, true) && !walk_takes_step(10, 1000, 3, true));
     for (int64_t W : {4, 16, 32, 48, 49, 128, 301, 1024, 30000})
